@@ -118,7 +118,8 @@ typedef struct {
 typedef struct {
     int32_t tess_level;    /* L, sub-triangles per patch L^2, 1..8 (default 4) */
     int32_t tile;          /* blending tile side: 8, 16 or 32 (default 16) */
-    int32_t batch;         /* Gaussians staged per LDS batch: 32, 64 or 128, at most tile*tile */
+    int32_t batch;         /* Gaussians staged per LDS batch: 32, 64 or 128, at most tile*tile (at 8 px
+                              32 are staged; 64 takes the variant with room for more boundary points) */
     int32_t flags;         /* BGT_FLAG_* bits (default 0) */
     float z_near;          /* cull distance along the optical axis (0.2) */
     float g_min;           /* Gaussian support: G >= g_min (2^-15) */
@@ -206,7 +207,7 @@ bgt_status bgt_render_bwd(bgt_ctx *ctx, const bgt_prims *prims, const bgt_views 
  * triangles (a bounding box over 256 pixels, or corners 2^17 pixels or more
  * apart on an axis), [6] tiles needing the global sort, [7] tiles whose boundary
  * list exceeded LDS, [8] tiles with more boundary runs (primitives) than
- * the forward's gamma* maps hold (their other runs are searched per pixel),
+ * the forward keeps weights of in LDS (the others' rows lie in memory),
  * [9] reserved (0).  Returns BGT_E_OVERFLOW when any overflow flag is set
  * (and clears the context's record of it). */
 bgt_status bgt_query(bgt_ctx *ctx, const void *state, size_t state_bytes, int64_t *counters,

@@ -498,8 +498,9 @@ bgt_status bgt_render_bwd(bgt_ctx *ctx, const bgt_prims *prims, const bgt_views 
     if (k.K > 0 && !gp.sh) return fail(ctx, BGT_E_INVALID, "null SH gradient array");
     hipError_t e = hipSuccess;
     const int64_t nc = 3LL * k.ncp * k.P;
-    {  // the gradient arrays are sums: they start at zero
+    {  // the gradient arrays are sums: they start at zero, as do the rows handed out
         ZeroTable z;
+        z.add(sp.counters + C_ROWS_BWD, 2);
         if (k.K > 0) z.add(gp.sh, 3LL * k.K * k.P);
         z.add(gp.ctrl, nc);
         z.add(gp.color, nc);

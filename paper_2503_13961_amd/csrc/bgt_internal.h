@@ -25,9 +25,9 @@ enum Counter {
     C_BIGTRI = 5,
     C_BIGSORT = 6,
     C_BIGBLIST = 7,
-    C_UNUSED8 = 8,
-    C_UNUSED9 = 9,
-    C_MANYRUNS = 10,  // tiles with more boundary runs than the forward's gamma* maps
+    C_ROWS_FWD = 8,   // gamma* rows handed out in memory by the forward, the backward
+    C_ROWS_BWD = 9,
+    C_MANYRUNS = 10,  // tiles with more boundary runs than the forward's gamma* rows in LDS
     C_NUM = 16
 };
 // The per-wave foreground and boundary tallies go to kStripes slots 64 bytes
