@@ -269,7 +269,7 @@ bgt_status loss_table(const bgt_views *vw, float lambda, LossTable &lt, int64_t 
     if (!(lambda >= 0.f && lambda <= 1.f)) return BGT_E_INVALID;
     memset(&lt, 0, sizeof(lt));
     lt.n = vw->n_views;
-    int64_t px = 0, tiles = 0;
+    int64_t px = 0, tiles = 0, sums = 0;
     for (int v = 0; v < vw->n_views; ++v) {
         const int W = vw->wh[2 * v], H = vw->wh[2 * v + 1];
         if (W < 1 || H < 1 || W > 16384 || H > 16384) return BGT_E_INVALID;
@@ -282,6 +282,7 @@ bgt_status loss_table(const bgt_views *vw, float lambda, LossTable &lt, int64_t 
         lt.px_off[v] = (int32_t)px;
         px += (int64_t)W * H;
         tiles += nt;
+        sums += (int64_t)((W + 31) / 32) * ((H + 15) / 16);  // (the workspace's size does not move with the tiles')
         if (px >= ((int64_t)1 << 30)) return BGT_E_INVALID;
     }
     lt.tile_off[vw->n_views] = (int32_t)tiles;
@@ -293,7 +294,7 @@ bgt_status loss_table(const bgt_views *vw, float lambda, LossTable &lt, int64_t 
     lt.inv_n = 1.0 / (3.0 * (double)px);
     lt.lam = lambda;
     maps_bytes = align256(3 * 3 * px * (int64_t)sizeof(float));
-    ws_bytes = maps_bytes + align256(2 * tiles * (int64_t)sizeof(double));
+    ws_bytes = maps_bytes + align256(2 * sums * (int64_t)sizeof(double));  // (at least one pair of sums per tile)
     return BGT_OK;
 }
 

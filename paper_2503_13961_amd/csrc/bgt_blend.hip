@@ -303,12 +303,14 @@ __device__ __forceinline__ int arg_min(const BL &B, const StatePtrs &st, int bs0
 }
 
 // The same for primitive g when it has no row (run table or pool full): its
-// part of the list is found first.
+// part of the list is taken from the table, or found first.
 template <typename BL>
-__device__ __forceinline__ int search_prim(const BL &B, const StatePtrs &st, int bs0, int bc, int g, int lx, int ly,
-                                           int ox, int oy, float *gam) {
-    const int e0 = first_of_prim(st, bs0, bc, g), e1 = first_of_prim(st, bs0, bc, g + 1);
-    return arg_min(B, st, bs0, e0, e1, 0, lx, ly, ox, oy, gam);
+__device__ __forceinline__ int search_prim(const BL &B, const StatePtrs &st, int bs0, int bc, int g, int n_runs, int lx,
+                                           int ly, int ox, int oy, float *gam) {
+    const int r = find_run(B.run_prim, n_runs, g);
+    const int e0 = r >= 0 ? B.run_start[r] : first_of_prim(st, bs0, bc, g);
+    const int e1 = r >= 0 ? B.run_start[r + 1] : first_of_prim(st, bs0, bc, g + 1);
+    return arg_min(B, st, bs0, e0, e1, bc <= BL::CAP ? bc : 0, lx, ly, ox, oy, gam);
 }
 
 // What a wave knows of its tile's runs after build_rows
@@ -734,7 +736,7 @@ __global__ void __launch_bounds__(TS *TS) k_blend_fwd(Consts k, ViewTable vt, St
                                 w = R.extra[(int64_t)(r - RM) * 64 + lane];
                             } else if (live && r == kSearch) {
                                 float gam;
-                                search_prim(B, st, bs0, bc, g, lx, ly, ox, oy, &gam);
+                                search_prim(B, st, bs0, bc, g, R.n_runs, lx, ly, ox, oy, &gam);
                                 w = weight(gam, own);
                             }
                         }
@@ -1031,7 +1033,7 @@ k_blend_bwd(Consts k, ViewTable vt, StatePtrs st, RowPool pool, const float *ima
         if constexpr (SEARCH)
             if (r == kSearch && live) {
                 float gam;
-                arg = search_prim(B, st, bs0, bc, g, lx, ly, ox, oy, &gam);
+                arg = search_prim(B, st, bs0, bc, g, R.n_runs, lx, ly, ox, oy, &gam);
                 w = weight(gam, g == h);
             }
         const float Gv = support_exp2(e);

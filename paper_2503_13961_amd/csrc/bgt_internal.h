@@ -252,7 +252,7 @@ __device__ __forceinline__ void zero_sums(float *g) {
 
 constexpr double kSsimC1 = 0.01 * 0.01, kSsimC2 = 0.03 * 0.03;
 
-// views of the loss pass: 32x16 output tiles, view-major
+// views of the loss pass: output tiles, view-major
 struct LossTable {
     int32_t n, total_tiles, total_px, pad;
     int32_t W[BGT_MAX_VIEWS], H[BGT_MAX_VIEWS], tiles_x[BGT_MAX_VIEWS];
