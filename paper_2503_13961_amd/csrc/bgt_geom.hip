@@ -381,7 +381,9 @@ __device__ __forceinline__ int wave_max_scan(int x) {
     return x;
 }
 
-// Set-ups of a wave's 64 triangles, for the lanes that rasterize their pixels.
+constexpr int64_t kRasterWaves = 4096;  // see launch_raster
+
+// Set-ups of a wave's triangles, for the lanes that rasterize their pixels.
 // (5 KB: eight waves' worth fit a CU's LDS four workgroups at a time)
 struct RasterWaveLds {
     int32_t start[64];      // first pixel of the triangle in the wave's pixel sequence
@@ -401,19 +403,24 @@ static_assert(sizeof(RasterWaveLds) == 5120, "four waves' set-ups in 20 KB");
 // lane over the concatenated boxes, so that lanes are not held by the
 // largest box of the wave.  Coverage and the z-buffer word are those of
 // raster_pixel (exact edge functions, here in FP64; FP64 1/z plane).
+// A wave takes `per_wave` triangles (a power of two up to 64), 64 where there
+// are enough to fill the chip: a launch of few triangles otherwise runs on a few
+// waves, each walking thousands of pixels (16 waves for 64 patches in one view,
+// 500 for 2000).
 __global__ void __launch_bounds__(256) k_raster(Consts k, ViewTable vt, const VertRec *verts,
-                                                unsigned long long *zbuf, int32_t *big, int64_t *counters) {
+                                                unsigned long long *zbuf, int32_t *big, int64_t *counters,
+                                                int per_wave) {
     __shared__ RasterWaveLds R[4];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     RasterWaveLds &Rw = R[wave];
     const int64_t per_view = (int64_t)k.L2 * k.P, n_tri = per_view * vt.n;
-    // lane l of the launch takes triangle group (l / 8) (2^31 - 1) mod
-    // n_groups, member l mod 8 (a permutation: 2^31 - 1 is a prime above the
+    // item i of the launch is member i mod 8 of triangle group (i / 8)
+    // (2^31 - 1) mod n_groups (a permutation: 2^31 - 1 is a prime above the
     // group count): a wave's eight groups come from all over the views, so
     // that the waves' pixel counts vary less than those of 64 neighbouring
     // patches, while each group's corner loads stay contiguous
-    const int64_t gi = blockIdx.x * (int64_t)blockDim.x + threadIdx.x, ng = (n_tri + 7) >> 3;
-    const int64_t idx = (gi >> 3) < ng ? ((gi >> 3) * 2147483647ll % ng) * 8 + (gi & 7) : n_tri;
+    const int64_t gi = (blockIdx.x * (int64_t)(blockDim.x >> 6) + wave) * per_wave + lane, ng = (n_tri + 7) >> 3;
+    const int64_t idx = lane < per_wave && (gi >> 3) < ng ? ((gi >> 3) * 2147483647ll % ng) * 8 + (gi & 7) : n_tri;
     int area = 0;
     if (idx < n_tri) {
         const int v = (int)(idx / per_view);
@@ -942,9 +949,14 @@ hipError_t launch_raster(const Consts &k, const ViewTable &vt, const PrimPtrs &p
                            (const double *)st.wverts, st.verts);
     }
     {
-        const int64_t n = (int64_t)vt.n * k.L2 * k.P;
-        hipLaunchKernelGGL(k_raster, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, k, vt,
-                           (const VertRec *)st.verts, st.zbuf, st.big_tris, st.counters);
+        const int64_t n = ((int64_t)vt.n * k.L2 * k.P + 7) / 8 * 8;  // (whole groups of 8)
+        // triangles per wave: 64 where that leaves the 1024 SIMDs four waves
+        // each to start with, else fewer
+        int per_wave = 64;
+        while (per_wave > 1 && n / per_wave < kRasterWaves) per_wave >>= 1;
+        const int64_t waves = (n + per_wave - 1) / per_wave;
+        hipLaunchKernelGGL(k_raster, dim3((unsigned)((waves + 3) / 4)), dim3(256), 0, s, k, vt,
+                           (const VertRec *)st.verts, st.zbuf, st.big_tris, st.counters, per_wave);
         hipLaunchKernelGGL(k_raster_big, dim3(1024), dim3(256), 0, s, k, vt, (const VertRec *)st.verts, st.zbuf,
                            (const int32_t *)st.big_tris, (const int64_t *)st.counters);
     }
