@@ -41,7 +41,7 @@ struct Shape {
     int64_t N, NT;
     int64_t NR;  // Gaussian records: the N pixel records, then the lattice Gaussians of every view
     int64_t off[BGT_STATE_FIELDS];
-    int64_t wverts_off, patch_off;
+    int64_t wverts_off, patch_off, gsum_off;
 };
 
 bgt_status fail(bgt_ctx *ctx, bgt_status st, const char *msg) {
@@ -91,6 +91,7 @@ bgt_status make_shape(bgt_ctx *ctx, const bgt_prims *pr, const bgt_views *vw, Sh
     k.T = pr->attr_res * (pr->attr_res + 1) / 2;
     k.K = (pr->sh_degree + 1) * (pr->sh_degree + 1) - 1;
     k.pdw = patch_dw(k.ncp, k.T, k.K);
+    k.gdw = (grad_words(k.ncp, k.T > 1 || k.K > 0) + 15) / 16 * 16;  // (whole 64-byte lines)
     k.lat_level = c.lattice >= 2 ? k.L * (c.lattice - 1) : 0;
     k.NL = c.lattice >= 2 ? (k.lat_level + 1) * (k.lat_level + 2) / 2 : 0;
     k.batch = c.batch;
@@ -157,7 +158,8 @@ bgt_status make_shape(bgt_ctx *ctx, const bgt_prims *pr, const bgt_views *vw, Sh
         sh.off[F_VERTS] = o;
         sh.wverts_off = align256(o + vbytes);
         sh.patch_off = align256(sh.wverts_off + wbytes);
-        o = align256(sh.patch_off + 4 * (int64_t)k.pdw * k.P);
+        sh.gsum_off = align256(sh.patch_off + 4 * (int64_t)k.pdw * k.P);
+        o = align256(sh.gsum_off + 4 * (int64_t)k.gdw * k.P);
     }
     put(F_GCOUNT, 4 * NT);
     put(F_GSTART, 4 * NT);
@@ -199,6 +201,7 @@ StatePtrs state_ptrs(const Shape &sh, void *state) {
     p.verts = (VertRec *)(b + sh.off[F_VERTS]);
     p.wverts = (double *)(b + sh.wverts_off);
     p.patch = (float *)(b + sh.patch_off);
+    p.gsum = (float *)(b + sh.gsum_off);
     p.g_count = (int32_t *)(b + sh.off[F_GCOUNT]);
     p.g_start = (int32_t *)(b + sh.off[F_GSTART]);
     p.g_cursor = (int32_t *)(b + sh.off[F_GCURSOR]);
@@ -498,17 +501,10 @@ bgt_status bgt_render_bwd(bgt_ctx *ctx, const bgt_prims *prims, const bgt_views 
     const Consts &k = sh.k;
     if (k.K > 0 && !gp.sh) return fail(ctx, BGT_E_INVALID, "null SH gradient array");
     hipError_t e = hipSuccess;
-    const int64_t nc = 3LL * k.ncp * k.P;
-    {  // the gradient arrays are sums: they start at zero, as do the rows handed out
+    {  // the patches' gradient sums start at zero, as do the rows handed out
         ZeroTable z;
         z.add(sp.counters + C_ROWS_BWD, 2);
-        if (k.K > 0) z.add(gp.sh, 3LL * k.K * k.P);
-        z.add(gp.ctrl, nc);
-        z.add(gp.color, nc);
-        z.add(gp.log_scale, 3LL * k.T * k.P);
-        z.add(gp.quat, 4LL * k.T * k.P);
-        z.add(gp.opacity, k.P);
-        z.add(gp.sharp, k.P);
+        z.add(sp.gsum, (int64_t)k.gdw * k.P);
         if ((e = launch_zero(z, st)) != hipSuccess) return hip_fail(ctx, e, "clear");
     }
     {

@@ -131,6 +131,7 @@ struct Consts {
     int32_t degree, ncp, P, T;
     int32_t batch, flags;  // flags: BGT_FLAG_* of the configuration
     int32_t K, pdw;        // SH coefficients per channel; dwords per patch record
+    int32_t gdw;           // dwords per patch of the gradient sums
     int32_t lat_level, NL; // lattice variant: level L (m - 1) and Gaussians per patch; NL = 0 otherwise
     float z_near, g_min, t_min, alpha_max, dilation, r_ref;
     float bg[3];
@@ -164,6 +165,11 @@ __host__ __device__ constexpr int patch_m_off(int ncp) { return 6 * ncp + 2; }
 __host__ __device__ constexpr int patch_q_off(int ncp) { return 6 * ncp + 22; }
 __host__ __device__ constexpr int patch_x_off(int ncp) { return 6 * ncp + 30; }
 __host__ __device__ constexpr int patch_sh_off(int ncp, int T) { return 6 * ncp + 30 + 7 * T; }
+
+// Words of a patch's gradient sums: control and colour points, log-scales and
+// quaternions of the texels, opacity, sharpness and SH coefficients, at the
+// largest attribute map and SH degree where a scene has either.
+__host__ __device__ constexpr int grad_words(int ncp, bool ext) { return 6 * ncp + (ext ? 7 * 6 + 2 + 3 * 15 : 9); }
 
 // per-view projected lattice vertex
 
@@ -206,6 +212,7 @@ struct StatePtrs {
     VertRec *verts;        // [V][VL][P]
     double *wverts;        // [VL][P][3] world lattice
     float *patch;          // [P][patch_dw(ncp)] packed per-patch record (see patch_dw)
+    float *gsum;           // [P][gdw] gradient sums of the backward (zeroed by each backward)
     int32_t *g_count, *g_start, *g_cursor;
     int32_t *b_count, *b_start, *b_cursor;
     unsigned long long *g_keys, *b_keys;

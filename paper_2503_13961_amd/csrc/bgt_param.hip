@@ -4,17 +4,28 @@
 //   dl/dp_ijk   = sum_q B^n_ijk(I_uv(q)) dl/dS_q     (Supplementary Sec. C)
 //   dl/dp^c_ijk = sum_q B^n_ijk(I_uv(q)) dl/dc_q     (Eq. 4)
 // plus log-scale, rotation, opacity and sharpness.  A workgroup covers a
-// 32x32 pixel region, its waves one 8x8 block at a time; pixels of the same
-// primitive are summed across the wave (segmented by primitive id) and the
-// wave sums across the region in an LDS table keyed by primitive, which
-// issues one global atomic per (region, primitive, parameter): the
-// primitives' gradient words are the hottest addresses of the pass, and
-// same-address atomics from many workgroups serialize.  In the lattice
-// variant a second launch walks the lattice Gaussians, 1024 consecutive
-// records (about a dozen patches) per workgroup, at their nodes' (u, v).
+// 32x32 pixel region, its waves one 8x8 block at a time.  A block's pixels
+// are written to LDS as rows in the order of their primitives, lane j walks a
+// primitive's rows and sums value j, and the sums of the region's blocks meet
+// in an LDS table keyed by primitive, from which one atomic per (region,
+// primitive, parameter) goes to the patch's words of the gradient sums: a
+// patch's words are consecutive, so a region's sums for it are three or four
+// 64-byte lines of atomics.  A last launch writes the gradient arrays, whose
+// rows run over the patches, from the sums.
+//
+// What bounds it, on 50000 patches in 32 views of 1024x768: atomics straight
+// into the gradient arrays touched 45 lines per patch and region (1.0 GB of
+// 32-byte writes, 2.24 ms); gathered per patch, 0.27 GB.  The reduction by
+// rows costs a pass over a block's 64 rows however many primitives it shows
+// (two LDS reads and one FMA per row); a reduce-scatter of the 45 values per
+// primitive cost 180 instructions each, with five primitives a block there.
+// Together 2.24 -> 1.28 ms; 2000 patches in 16 views of 800x800 0.326 ->
+// 0.30 ms, where the waits for the scattered 36-byte sums remain.  In the
+// lattice variant a second launch walks the lattice Gaussians, 1024
+// consecutive records (about a dozen patches) per workgroup, at their nodes'
+// (u, v).
 #include "bgt_internal.h"
 #include "bgt_sh.h"
-#include "bgt_wave.h"
 
 namespace bgt {
 
@@ -39,47 +50,52 @@ __device__ __forceinline__ void bern_f(float u, float v, float w, float *B) {
         }
 }
 
-// One chunk of up to 64 of a wave's NV per-lane values (from `value`, taken
-// on the lanes where `mine`): reduce-scattered over the wave, then each lane
-// holding a total adds it to row `slot` of the workgroup's LDS table, or,
-// without a row (the table is full), to its global target.
-template <int BASE, int NV, typename V, typename T>
-__device__ __forceinline__ void reduce_chunk(V &value, T &target, bool mine, int gl, int lane, float *table,
-                                             int slot) {
-    constexpr int N = NV - BASE < 64 ? NV - BASE : 64;
-    float v[N];
-#pragma unroll
-    for (int i = 0; i < N; ++i) v[i] = mine ? value(BASE + i) : 0.f;
-    wave_reduce_scatter<N>(v, lane);
-    const int j = BASE + scatter_index(lane);
-    if (j < BASE + N && v[0] != 0.f) {
-        if (slot >= 0) {
-            atomicAdd(&table[slot * NV + j], v[0]);
-        } else {
-            float *t = target(j, gl);
-            if (t) unsafeAtomicAdd(t, v[0]);
-        }
-    }
-}
+// A pixel's row in LDS: the factors of its NV values, each value a product of
+// two words (a plain value's second factor is the word 1).  The rows of one
+// primitive are consecutive; lane j walks them and sums value j.
+template <int NCP, bool EXT>
+struct RowDims {
+    // texels of the rotation and scale maps (at most 6), SH coefficients (at most 15 per channel)
+    static constexpr int TM = EXT ? 6 : 1, KM = EXT ? 15 : 0;
+    // Bernstein weights, dl/dS, dl/dc, [texel weights,] dl/dlog-scale,
+    // dl/dquaternion, dl/dopacity, dl/dsharpness, [SH basis,] 1
+    static constexpr int S = NCP, C = S + 3, T = C + 3, L = T + (EXT ? TM : 0), Q = L + 3, O = Q + 4, H = O + 1, Y = H + 1,
+                         ONE = Y + KM, WORDS = ONE + 1;
+    // words per row: whole 16-byte stores, and eight rows' stores on different banks
+    static constexpr int STRIDE = (WORDS + 3) / 4 * 4 + ((WORDS + 3) / 4 * 4 % 16 == 0 ? 4 : 0);
+    static constexpr int ROWS = 64 + 3;  // (a primitive's last group of four rows may reach past row 63)
+    // values: control points [d][c], colour control points [d][c], log-scales
+    // [d][t], quaternions [d][t], opacity, sharpness, SH coefficients [c][j]
+    static constexpr int NV = grad_words(NCP, EXT);
+    static_assert(NV == 6 * NCP + 7 * TM + 2 + 3 * KM, "one word per value");
+    static constexpr int CHUNKS = (NV + 63) / 64;
 
-// Row of primitive p (wave-uniform) in the workgroup's table: open
-// addressing over the rows' primitive ids, claimed by compare-and-swap;
-// -1 when every row holds another primitive.
-template <int SLOTS>
-__device__ __forceinline__ int table_slot(int *slot_prim, int p, int lane) {
-    int s = -1;
-    if (lane == 0) {
-        const int h = (int)(((unsigned)p * 2654435761u) >> 16) & (SLOTS - 1);
-        for (int n = 0; n < SLOTS; ++n) {
-            const int q = (h + n) & (SLOTS - 1);
-            const int old = atomicCAS(&slot_prim[q], -1, p);
-            if (old == -1 || old == p) {
-                s = q;
-                break;
-            }
-        }
+    static __device__ __forceinline__ void factors(int j, int &a, int &b) {
+        const int r = j - 6 * NCP, h = r - 7 * TM - 2;
+        b = ONE;
+        if (j < 3 * NCP) { a = j % NCP; b = S + j / NCP; }
+        else if (r < 0) { a = (j - 3 * NCP) % NCP; b = C + (j - 3 * NCP) / NCP; }
+        else if (r < 3 * TM) { a = L + r / TM; if (EXT) b = T + r % TM; }
+        else if (r < 7 * TM) { a = Q + (r - 3 * TM) / TM; if (EXT) b = T + (r - 3 * TM) % TM; }
+        else if (h < 0) a = O + (r - 7 * TM);
+        else { a = Y + h % (KM > 0 ? KM : 1); b = C + h / (KM > 0 ? KM : 1); }
     }
-    return __builtin_amdgcn_readfirstlane(s);
+};
+
+// Row of primitive p in the workgroup's table, each lane for its own p: open
+// addressing over the rows' primitive ids, claimed by compare-and-swap; -1
+// when kProbes rows from its hash on hold other primitives.
+constexpr int kProbes = 16;
+
+template <int SLOTS>
+__device__ __forceinline__ int table_slot(int *slot_prim, int p) {
+    const int h = (int)(((unsigned)p * 2654435761u) >> 16);
+    for (int n = 0; n < kProbes; ++n) {
+        const int q = (h + n) & (SLOTS - 1);
+        const int old = atomicCAS(&slot_prim[q], -1, p);
+        if (old == -1 || old == p) return q;
+    }
+    return -1;
 }
 
 constexpr int kRegion = 32;      // pixels per side of a workgroup's region
@@ -111,7 +127,8 @@ __device__ __forceinline__ int region_view(const ViewTable &vt, int reg, int &rx
 // lies before the end of the tile's replayed prefix: the backward writes
 // every entry of that prefix and no other.  The tiles are taken three at a
 // time with every load issued before any is used (a slot past the prefix is
-// loaded and not added), so a record of up to three tiles waits for one
+// loaded and not added; a tile past the range is not loaded, whose lines were a
+// tenth of the pass's time), so a record of up to three tiles waits for one
 // round trip.  A wide record's sums were added into its own floats, which are
 // read and cleared for the next backward pass.  `ovf`: lists overflowed their
 // capacity and lack entries, whose slots hold no position of this pass; no
@@ -136,61 +153,58 @@ __device__ __forceinline__ void gauss_sums(const Consts &k, const ViewInfo &vi, 
         float q[3][kSums];
 #pragma unroll
         for (int c = 0; c < 3; ++c) {
-            const int j = min(j0 + c, nt - 1);  // (past the range: the last tile again, not added)
-            const int tx = gt0 + j % nx, ty = gu0 + j / nx;
-            const int64_t si = (int64_t)tile_slot(tx, ty) * st.n_rec + rid;
-            p[c] = st.gpos[si];
-            e[c] = st.t_end[vi.tile_off + ty * vi.tiles_x + tx];
+            p[c] = 0;
+            e[c] = 0;
 #pragma unroll
-            for (int f = 0; f < kSums; ++f) q[c][f] = st.gslot[si * kSums + f];
+            for (int f = 0; f < kSums; ++f) q[c][f] = 0.f;
+            const int j = j0 + c;
+            if (j < nt) {
+                const int tx = gt0 + j % nx, ty = gu0 + j / nx;
+                const int64_t si = (int64_t)tile_slot(tx, ty) * st.n_rec + rid;
+                p[c] = st.gpos[si];
+                e[c] = st.t_end[vi.tile_off + ty * vi.tiles_x + tx];
+#pragma unroll
+                for (int f = 0; f < kSums; ++f) q[c][f] = st.gslot[si * kSums + f];
+            }
         }
 #pragma unroll
         for (int c = 0; c < 3; ++c) {
-            const bool ok = j0 + c < nt && p[c] < e[c];
+            const bool ok = p[c] < e[c];
 #pragma unroll
             for (int f = 0; f < kSums; ++f) g[f] += ok ? q[c][f] : 0.f;
         }
     }
 }
 
+// (waves per SIMD: as many as the registers allow without spilling)
 template <int DEG, bool EXT, bool LAT>
-__global__ void __launch_bounds__(256) k_param_bwd(Consts k, ViewTable vt, PrimPtrs pr, const float *cams,
-                                                  StatePtrs st, GradPtrs gr, const float *__restrict__ patch) {
+__global__ void __launch_bounds__(256, EXT ? 2 : DEG <= 2 ? 4 : 3) k_param_bwd(Consts k, ViewTable vt, PrimPtrs pr, const float *cams,
+                                                                    StatePtrs st, const float *__restrict__ patch) {
     constexpr int NCP = (DEG + 1) * (DEG + 2) / 2;
     constexpr int QO = patch_q_off(NCP);
     const int PD = k.pdw;
-    // values per pixel: control points, colour control points, log-scales and
-    // quaternions of the map's texels (at most 6), opacity, sharpness, SH
-    // coefficients (at most 15 per channel)
-    constexpr int TM = EXT ? 6 : 1, KM = EXT ? 15 : 0;
-    constexpr int NV = 6 * NCP + 7 * TM + 2 + 3 * KM;
+    using RD = RowDims<NCP, EXT>;
+    constexpr int TM = RD::TM, KM = RD::KM, NV = RD::NV, CH = RD::CHUNKS;
     constexpr int SLOTS = NV > 100 ? 32 : 64;
     __shared__ int slot_prim[SLOTS];
     __shared__ float table[SLOTS * NV];
+    __shared__ __attribute__((aligned(16))) float stage[4][RD::ROWS * RD::STRIDE];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    float *rows = stage[wave];
+    const float *fa[CH], *fb[CH];  // this lane's factors in row 0, per chunk of 64 values
+#pragma unroll
+    for (int ch = 0; ch < CH; ++ch) {
+        int a, b;
+        RD::factors(min(64 * ch + lane, NV - 1), a, b);
+        fa[ch] = rows + a;
+        fb[ch] = rows + b;
+    }
     const bool ovf = (st.counters[C_OVERFLOW] & 1) != 0;  // the Gaussian lists overflowed
     for (int i = threadIdx.x; i < SLOTS; i += blockDim.x) slot_prim[i] = -1;
     for (int i = threadIdx.x; i < SLOTS * NV; i += blockDim.x) table[i] = 0.f;
     int rx0 = 0, ry0 = 0, rv = 0;
     if constexpr (!LAT) rv = region_view(vt, blockIdx.x, rx0, ry0);
     __syncthreads();
-    auto target = [&](int j, int gl) -> float * {
-        if (j < 3 * NCP) return gr.ctrl + (int64_t)j * k.P + gl;  // [d][c] with j = d NCP + c
-        if (j < 6 * NCP) return gr.color + (int64_t)(j - 3 * NCP) * k.P + gl;
-        const int r = j - 6 * NCP;
-        if (r < 3 * TM) {
-            const int d = r / TM, t = r % TM;
-            return t < k.T ? gr.log_scale + ((int64_t)d * k.T + t) * k.P + gl : nullptr;
-        }
-        if (r < 7 * TM) {
-            const int d = (r - 3 * TM) / TM, t = (r - 3 * TM) % TM;
-            return t < k.T ? gr.quat + ((int64_t)d * k.T + t) * k.P + gl : nullptr;
-        }
-        if (r == 7 * TM) return gr.opacity + gl;
-        if (r == 7 * TM + 1) return gr.sharp + gl;
-        const int h = r - 7 * TM - 2, c = h / (KM > 0 ? KM : 1), jj = h % (KM > 0 ? KM : 1);
-        return jj < k.K ? gr.sh + ((int64_t)c * k.K + jj) * k.P + gl : nullptr;
-    };
 #pragma unroll 1
     for (int pass = 0; pass < kRegionPasses; ++pass) {
     // locate the view and pixel (or lattice record) of this lane
@@ -210,6 +224,7 @@ __global__ void __launch_bounds__(256) k_param_bwd(Consts k, ViewTable vt, PrimP
     float g[12];
 #pragma unroll
     for (int i = 0; i < 12; ++i) g[i] = 0.f;
+    float cp[3 * NCP], raw[8];  // the patch's control points, quaternion, log-scales and sharpness
     int v0 = 0;  // view of the lane's record
     float2 uv = make_float2(0.f, 0.f);
     if constexpr (LAT) {
@@ -249,6 +264,7 @@ __global__ void __launch_bounds__(256) k_param_bwd(Consts k, ViewTable vt, PrimP
                 tri = st.I_tri[pix];
                 uvp = st.I_uv[pix];
             }
+            if constexpr (!LAT) prim = tri / k.L2;
             if (LAT || k.NL == 0) gauss_sums(k, vt.v[v0], st, pix, ovf, g);
             if (!LAT && (fl & PF_BOUNDARY)) {  // read and cleared for the next backward pass
                 float *bp = st.dbound + (int64_t)pix * 3;
@@ -260,30 +276,8 @@ __global__ void __launch_bounds__(256) k_param_bwd(Consts k, ViewTable vt, PrimP
             for (int i = 0; i < 12; ++i) nz = nz || g[i] != 0.f;
             if (nz) {
                 act = true;
-                if constexpr (!LAT) {
-                    prim = tri / k.L2;
-                    uv = uvp;
-                }
+                if constexpr (!LAT) uv = uvp;
             }
-        }
-    }
-    // the patches of this wave through the scalar unit: the wave walks its
-    // distinct ids and each lane keeps its own patch's points and attributes
-    float cp[3 * NCP], raw[8];
-#pragma unroll
-    for (int i = 0; i < 3 * NCP; ++i) cp[i] = 0.f;
-#pragma unroll
-    for (int i = 0; i < 8; ++i) raw[i] = 0.f;
-    for (unsigned long long todo = __ballot(act); todo;) {
-        const int pu = __builtin_amdgcn_readlane(prim, __ffsll((long long)todo) - 1);
-        const bool mine = act && prim == pu;
-        todo &= ~__ballot(mine);
-        const float *src = patch + (int64_t)pu * PD;
-        if (mine) {
-#pragma unroll
-            for (int i = 0; i < 3 * NCP; ++i) cp[i] = src[i];
-#pragma unroll
-            for (int i = 0; i < 8; ++i) raw[i] = src[QO + i];
         }
     }
     {
@@ -295,6 +289,14 @@ __global__ void __launch_bounds__(256) k_param_bwd(Consts k, ViewTable vt, PrimP
             const float dsig = g[9], dbx = g[10], dby = g[11];
             {
                 const int p = prim;
+                // the patch's points and attributes, per lane: a block at a
+                // silhouette shows tens of patches (loaded here and not with the
+                // blend sums, where their 26 registers made the kernel spill)
+                const float *src = patch + (int64_t)prim * PD;
+#pragma unroll
+                for (int i = 0; i < 3 * NCP; ++i) cp[i] = src[i];
+#pragma unroll
+                for (int i = 0; i < 8; ++i) raw[i] = src[QO + i];
                 bern_f<DEG>(uv.x, uv.y, 1.f - uv.x - uv.y, B);
                 float S[3] = {0.f, 0.f, 0.f};
 #pragma unroll
@@ -479,31 +481,91 @@ __global__ void __launch_bounds__(256) k_param_bwd(Consts k, ViewTable vt, PrimP
             }
         }
     }
-    // per primitive present in the wave: a reduce-scatter of its NV sums over
-    // the wave, then one multi-lane atomic add per 64 values
-    // value order: ctrl [d][c], colour [d][c], log-scale [d][t], quaternion
-    // [d][t], opacity, sharpness, SH [c][j]
-    auto value = [&](int j) -> float {  // j is a compile-time constant after unrolling
-        if (j < 3 * NCP) return B[j % NCP] * dS[j / NCP];
-        if (j < 6 * NCP) return B[(j - 3 * NCP) % NCP] * dcol[(j - 3 * NCP) / NCP];
-        const int r = j - 6 * NCP;
-        if (r < 3 * TM) return EXT ? dls[r / TM] * tw6[r % TM] : dls[r];
-        if (r < 7 * TM) return EXT ? dq[(r - 3 * TM) / TM] * tw6[(r - 3 * TM) % TM] : dq[r - 3];
-        if (r == 7 * TM) return dop;
-        if (r == 7 * TM + 1) return dsh;
-        const int h = r - 7 * TM - 2;
-        return KM > 0 ? Yv[h % (KM > 0 ? KM : 1)] * dcol[h / (KM > 0 ? KM : 1)] : 0.f;
-    };
-    for (unsigned long long pending = __ballot(act); pending;) {
-        const int gl = __builtin_amdgcn_readlane(prim, __ffsll((long long)pending) - 1);
+    // the wave's primitives: first lane, number of lanes, and each lane's row
+    // in the order of the primitives
+    unsigned long long leaders = 0ull;
+    int row = 0, cnt = 0, slot = -1, n_rows = 0;
+    for (unsigned long long todo = __ballot(act); todo;) {
+        const int l = __ffsll((long long)todo) - 1;
+        const int gl = __builtin_amdgcn_readlane(prim, l);
         const bool mine = act && prim == gl;
-        pending &= ~__ballot(mine);
-        const int slot = table_slot<SLOTS>(slot_prim, gl, lane);
-        reduce_chunk<0, NV>(value, target, mine, gl, lane, table, slot);
-        if constexpr (NV > 64) reduce_chunk<64, NV>(value, target, mine, gl, lane, table, slot);
-        if constexpr (NV > 128) reduce_chunk<128, NV>(value, target, mine, gl, lane, table, slot);
-        if constexpr (NV > 192) reduce_chunk<192, NV>(value, target, mine, gl, lane, table, slot);
+        const unsigned long long m = __ballot(mine);
+        todo &= ~m;
+        leaders |= 1ull << l;
+        const int before = (int)__builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, (unsigned)n_rows));
+        if (mine) {
+            row = before;
+            cnt = __popcll(m);
+        }
+        n_rows += __popcll(m);
     }
+    if ((leaders >> lane) & 1) slot = table_slot<SLOTS>(slot_prim, prim);
+    if (act) {
+        float w[RD::STRIDE];
+#pragma unroll
+        for (int i = 0; i < RD::STRIDE; ++i) w[i] = 0.f;
+#pragma unroll
+        for (int i = 0; i < NCP; ++i) w[i] = B[i];
+#pragma unroll
+        for (int i = 0; i < 3; ++i) { w[RD::S + i] = dS[i]; w[RD::C + i] = dcol[i]; w[RD::L + i] = dls[i]; }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) w[RD::Q + i] = dq[i];
+        if constexpr (EXT) {
+#pragma unroll
+            for (int t = 0; t < TM; ++t) w[RD::T + t] = tw6[t];
+#pragma unroll
+            for (int j = 0; j < KM; ++j) w[RD::Y + j] = Yv[j];
+        }
+        w[RD::O] = dop;
+        w[RD::H] = dsh;
+        w[RD::ONE] = 1.f;
+        float4 *o = (float4 *)(rows + row * RD::STRIDE);
+#pragma unroll
+        for (int i = 0; i < (RD::WORDS + 3) / 4; ++i) o[i] = make_float4(w[4 * i], w[4 * i + 1], w[4 * i + 2], w[4 * i + 3]);
+    }
+    // (LDS operations of one wave complete in order: the fences keep the
+    // compiler from moving them across each other)
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    // lane j sums value j over the primitive's rows, four at a time, and adds
+    // it to the primitive's row of the table, or, without a row, to its
+    // global target
+    int r0 = 0;
+    for (; leaders; leaders &= leaders - 1) {
+        const int l = __ffsll((long long)leaders) - 1;
+        const int gl = __builtin_amdgcn_readlane(prim, l), n = __builtin_amdgcn_readlane(cnt, l);
+        const int sl = __builtin_amdgcn_readlane(slot, l);
+#pragma unroll
+        for (int ch = 0; ch < CH; ++ch) {
+            const float *pa = fa[ch] + r0 * RD::STRIDE, *pb = fb[ch] + r0 * RD::STRIDE;
+            float s0 = 0.f, s1 = 0.f, s2 = 0.f, s3 = 0.f;
+            int i = 0;
+            for (; i + 4 <= n; i += 4) {
+                s0 += pa[0] * pb[0];
+                s1 += pa[RD::STRIDE] * pb[RD::STRIDE];
+                s2 += pa[2 * RD::STRIDE] * pb[2 * RD::STRIDE];
+                s3 += pa[3 * RD::STRIDE] * pb[3 * RD::STRIDE];
+                pa += 4 * RD::STRIDE;
+                pb += 4 * RD::STRIDE;
+            }
+            if (i < n) {  // (one to three rows left; the rows after them are read and not added)
+                const float v0 = pa[0] * pb[0], v1 = pa[RD::STRIDE] * pb[RD::STRIDE];
+                const float v2 = pa[2 * RD::STRIDE] * pb[2 * RD::STRIDE];
+                s0 += v0;
+                s1 += i + 1 < n ? v1 : 0.f;
+                s2 += i + 2 < n ? v2 : 0.f;
+            }
+            const float sum = (s0 + s1) + (s2 + s3);
+            const int j = 64 * ch + lane;
+            if (j < NV && sum != 0.f) {
+                if (sl >= 0) atomicAdd(&table[sl * NV + j], sum);
+                else unsafeAtomicAdd(&st.gsum[(int64_t)gl * k.gdw + j], sum);
+            }
+        }
+        r0 += n;
+    }
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+    __builtin_amdgcn_wave_barrier();
     }  // passes
     // the region's sums: one global atomic per (primitive, parameter)
     __syncthreads();
@@ -511,10 +573,43 @@ __global__ void __launch_bounds__(256) k_param_bwd(Consts k, ViewTable vt, PrimP
         const int s = i / NV, j = i - s * NV;
         const int p = slot_prim[s];
         const float val = table[i];
-        if (p >= 0 && val != 0.f) {
-            float *t = target(j, p);
-            if (t) unsafeAtomicAdd(t, val);
+        if (p >= 0 && val != 0.f) unsafeAtomicAdd(&st.gsum[(int64_t)p * k.gdw + j], val);
+    }
+}
+
+// The gradient arrays (patch index fastest) from the per-patch sums: a
+// workgroup transposes 16 words of 64 patches through LDS, so that the arrays'
+// rows are written and the sums' lines read whole.
+__global__ void __launch_bounds__(256) k_grad_out(Consts k, const float *gsum, GradPtrs gr) {
+    __shared__ float tile[64][17];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int p0 = blockIdx.x * 64, np = min(64, k.P - p0), j0 = blockIdx.y * 16;
+    const bool ext = k.T > 1 || k.K > 0;
+    const int TM = ext ? 6 : 1, KM = ext ? 15 : 1, nv = grad_words(k.ncp, ext);
+    const int r0 = 6 * k.ncp, h0 = r0 + 7 * TM + 2;
+#pragma unroll
+    for (int i = threadIdx.x >> 4; i < 64; i += 16)  // (the row's words reach to gdw, a multiple of 16)
+        if (i < np) tile[i][threadIdx.x & 15] = gsum[(int64_t)(p0 + i) * k.gdw + j0 + (threadIdx.x & 15)];
+    __syncthreads();
+#pragma unroll
+    for (int jj = wave; jj < 16; jj += 4) {
+        const int j = j0 + jj;
+        float *t = nullptr;
+        int64_t row = 0;
+        if (j < 3 * k.ncp) { t = gr.ctrl; row = j; }  // [d][c] with j = d ncp + c
+        else if (j < r0) { t = gr.color; row = j - 3 * k.ncp; }
+        else if (j < r0 + 7 * TM) {  // log-scales, then quaternions, [d][t]
+            const int d = (j - r0) / TM, e = (j - r0) % TM;
+            t = e >= k.T ? nullptr : d < 3 ? gr.log_scale : gr.quat;
+            row = (int64_t)(d < 3 ? d : d - 3) * k.T + e;
+        } else if (j == h0 - 2) t = gr.opacity;
+        else if (j == h0 - 1) t = gr.sharp;
+        else if (j < nv) {  // SH coefficients [c][j]
+            const int c = (j - h0) / KM, e = (j - h0) % KM;
+            t = e >= k.K ? nullptr : gr.sh;
+            row = (int64_t)c * k.K + e;
         }
+        if (t && lane < np) t[row * k.P + p0 + lane] = tile[lane][jj];
     }
 }
 
@@ -528,7 +623,7 @@ hipError_t launch_param_bwd(const Consts &k, const ViewTable &vt, const PrimPtrs
     for (int lat = 0; lat < (k.NL > 0 ? 2 : 1); ++lat) {
         const int64_t groups = lat ? ((int64_t)vt.n * k.P * k.NL + kLatPerGroup - 1) / kLatPerGroup : regions;
         dim3 grid((unsigned)groups), block(256);
-#define BGT_PB(D, E, LT) hipLaunchKernelGGL((k_param_bwd<D, E, LT>), grid, block, 0, s, k, vt, pr, cams, st, gr, st.patch)
+#define BGT_PB(D, E, LT) hipLaunchKernelGGL((k_param_bwd<D, E, LT>), grid, block, 0, s, k, vt, pr, cams, st, st.patch)
 #define BGT_PB_CASE(D)                                  \
     case D:                                             \
         if (lat) {                                      \
@@ -546,6 +641,8 @@ hipError_t launch_param_bwd(const Consts &k, const ViewTable &vt, const PrimPtrs
 #undef BGT_PB_CASE
 #undef BGT_PB
     }
+    hipLaunchKernelGGL(k_grad_out, dim3((unsigned)((k.P + 63) / 64), (unsigned)(k.gdw / 16)), dim3(256), 0, s, k,
+                       (const float *)st.gsum, gr);
     return hipGetLastError();
 }
 
