@@ -118,12 +118,6 @@ __global__ void __launch_bounds__(kScanThreads) k_scan_down(int32_t *gc, int32_t
 
 // ------------------------------------------------------------ scatter
 
-// A lane's tile rectangle [x0, x1] x [y0, y1] (empty: x0 > x1).
-struct TileRect {
-    int x0 = 1, x1 = 0, y0 = 1, y1 = 0;
-    __device__ bool has(int tx, int ty) const { return tx >= x0 && tx <= x1 && ty >= y0 && ty <= y1; }
-};
-
 // The pairs of the lanes whose rectangles lie within the 3x3 tiles around
 // (cx, cy), the tile of the wave's 8x8 block, for both lists: one cursor
 // atomic per (list, neighbouring tile) for the whole wave, all issued by one
@@ -139,15 +133,12 @@ template <typename EG, typename EB>
 __device__ __forceinline__ void near_tiles(bool gin, const TileRect &g, bool bin, const TileRect &b, int cx, int cy,
                                            const ViewInfo &vi, const StatePtrs &st, int lane, EG &&emit_g,
                                            EB &&emit_b) {
-    const unsigned long long below = (1ull << lane) - 1ull;
+    const NearMasks mg(gin, g, cx, cy), mb(bin, b, cx, cy);
     int cnt = 0;
 #pragma unroll
     for (int j = 0; j < 9; ++j) {
-        const int tx = cx + j % 3 - 1, ty = cy + j / 3 - 1;
-        const unsigned long long mg = __ballot(gin && g.has(tx, ty));
-        const unsigned long long mb = __ballot(bin && b.has(tx, ty));
-        if (lane == j) cnt = __popcll(mg);
-        if (lane == 9 + j) cnt = __popcll(mb);
+        if (lane == j) cnt = __popcll(mg.at(j));
+        if (lane == 9 + j) cnt = __popcll(mb.at(j));
     }
     int base = 0, s0 = 0, c0 = 0;
     if (cnt > 0) {
@@ -165,14 +156,15 @@ __device__ __forceinline__ void near_tiles(bool gin, const TileRect &g, bool bin
         bs[j] = __builtin_amdgcn_readlane(base, j);
         es[j] = __builtin_amdgcn_readlane(end, j);
     }
+    auto slot_in = [](unsigned long long m, int first) {  // the lane's rank among the lanes of m, from `first`
+        return (int)__builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, (unsigned)first));
+    };
 #pragma unroll
     for (int j = 0; j < 9; ++j) {
-        const int tx = cx + j % 3 - 1, ty = cy + j / 3 - 1;
-        const bool ig = gin && g.has(tx, ty), ib = bin && b.has(tx, ty);
-        const unsigned long long mg = __ballot(ig), mb = __ballot(ib);
-        const int sg = bs[j] + __popcll(mg & below), sb = bs[9 + j] + __popcll(mb & below);
-        if (ig && sg < es[j]) emit_g(sg);
-        if (ib && sb < es[9 + j]) emit_b(sb);
+        const unsigned long long ig = mg.at(j), ib = mb.at(j);
+        const int sg = slot_in(ig, bs[j]), sb = slot_in(ib, bs[9 + j]);
+        if (__builtin_amdgcn_inverse_ballot_w64(ig) && sg < es[j]) emit_g(sg);
+        if (__builtin_amdgcn_inverse_ballot_w64(ib) && sb < es[9 + j]) emit_b(sb);
     }
 }
 
@@ -215,10 +207,7 @@ __global__ void __launch_bounds__(256) k_scatter(Consts k, ViewTable vt, StatePt
     // rectangles within the 3x3 tiles around the block's tile (nearly all):
     // one round of cursor atomics for both lists; the rest one cursor atomic
     // per group of lanes at the same tile, each lane taking the slot of its rank
-    const bool gnear = g.x0 <= g.x1 && g.y0 <= g.y1 && g.x0 >= cx - 1 && g.x1 <= cx + 1 && g.y0 >= cy - 1 &&
-                       g.y1 <= cy + 1;
-    const bool bnear = b.x0 <= b.x1 && b.y0 <= b.y1 && b.x0 >= cx - 1 && b.x1 <= cx + 1 && b.y0 >= cy - 1 &&
-                       b.y1 <= cy + 1;
+    const bool gnear = g.near(cx, cy), bnear = b.near(cx, cy);
     near_tiles(gnear, g, bnear, b, cx, cy, vi, st, lane, [&](int slot) { st.g_keys[slot] = gkey; },
                [&](int slot) { st.b_keys[slot] = bkey; });
     const unsigned long long below = (1ull << lane) - 1ull;
@@ -228,7 +217,7 @@ __global__ void __launch_bounds__(256) k_scatter(Consts k, ViewTable vt, StatePt
                       [&](int t, unsigned long long gm, bool in, int leader) {
         int base = 0;
         if (lane == leader) base = atomicAdd(&st.g_cursor[t], __popcll(gm));
-        base = __shfl(base, leader, 64);
+        base = __builtin_amdgcn_readlane(base, leader);
         if (in) {
             const int slot = base + __popcll(gm & below);
             if (slot < st.g_start[t] + st.g_count[t]) st.g_keys[slot] = gkey;
@@ -238,7 +227,7 @@ __global__ void __launch_bounds__(256) k_scatter(Consts k, ViewTable vt, StatePt
                       [&](int t, unsigned long long gm, bool in, int leader) {
         int base = 0;
         if (lane == leader) base = atomicAdd(&st.b_cursor[t], __popcll(gm));
-        base = __shfl(base, leader, 64);
+        base = __builtin_amdgcn_readlane(base, leader);
         if (in) {
             const int slot = base + __popcll(gm & below);
             if (slot < st.b_start[t] + st.b_count[t]) st.b_keys[slot] = bkey;
@@ -280,7 +269,7 @@ __global__ void __launch_bounds__(256) k_scatter_lattice(Consts k, ViewTable vt,
         const int cx = __builtin_amdgcn_readlane((gt0 + gt1) >> 1, f);
         const int cy = __builtin_amdgcn_readlane((gu0 + gu1) >> 1, f);
         const int vw = __builtin_amdgcn_readlane(v, f);
-        const bool near = gt0 <= gt1 && v == vw && gt0 >= cx - 1 && gt1 <= cx + 1 && gu0 >= cy - 1 && gu1 <= cy + 1;
+        const bool near = v == vw && g.near(cx, cy);
         near_tiles(near, g, false, TileRect(), cx, cy, vt.v[vw], st, lane, [&](int slot) { st.g_keys[slot] = gkey; },
                    [&](int) {});
         if (near) g = TileRect();
@@ -290,7 +279,7 @@ __global__ void __launch_bounds__(256) k_scatter_lattice(Consts k, ViewTable vt,
                       [&](int t, unsigned long long gm, bool in, int leader) {
         int base = 0;
         if (lane == leader) base = atomicAdd(&st.g_cursor[t], __popcll(gm));
-        base = __shfl(base, leader, 64);
+        base = __builtin_amdgcn_readlane(base, leader);
         if (in) {
             const int slot = base + __popcll(gm & below);
             if (slot < st.g_start[t] + st.g_count[t]) st.g_keys[slot] = gkey;

@@ -101,7 +101,7 @@ __device__ __forceinline__ void for_tiles_grouped(int tx0, int tx1, int ty0, int
         if (!am) break;
         const int mine = alive ? tile_off + cy * tiles_x + cx : -1;
         const int leader = __ffsll((long long)am) - 1;
-        const int t0 = __shfl(mine, leader, 64);
+        const int t0 = __builtin_amdgcn_readlane(mine, leader);
         const bool in = alive && mine == t0;
         const unsigned long long gm = __ballot(in);
         f(t0, gm, in, leader);
@@ -110,6 +110,32 @@ __device__ __forceinline__ void for_tiles_grouped(int tx0, int tx1, int ty0, int
         }
     }
 }
+
+// A lane's tile rectangle [x0, x1] x [y0, y1] (empty: x0 > x1).
+struct TileRect {
+    int x0 = 1, x1 = 0, y0 = 1, y1 = 0;
+    // not empty and within the 3x3 tiles around (cx, cy)
+    __device__ bool near(int cx, int cy) const {
+        return x0 <= x1 && y0 <= y1 && x0 >= cx - 1 && x1 <= cx + 1 && y0 >= cy - 1 && y1 <= cy + 1;
+    }
+};
+
+// The lanes at each of the 3x3 tiles around (cx, cy), of the lanes where
+// `in`: one mask per tile column and row, a tile's lanes are their
+// intersection (9 scalar operations for the 9 tiles; comparing per tile took
+// 4 vector operations each).
+struct NearMasks {
+    unsigned long long col[3], row[3];
+    __device__ __forceinline__ NearMasks(bool in, const TileRect &r, int cx, int cy) {
+        const unsigned long long m = __ballot(in);
+#pragma unroll
+        for (int j = 0; j < 3; ++j) {
+            col[j] = m & __builtin_amdgcn_ballot_w64(r.x0 <= cx - 1 + j) & __builtin_amdgcn_ballot_w64(r.x1 >= cx - 1 + j);
+            row[j] = m & __builtin_amdgcn_ballot_w64(r.y0 <= cy - 1 + j) & __builtin_amdgcn_ballot_w64(r.y1 >= cy - 1 + j);
+        }
+    }
+    __device__ __forceinline__ unsigned long long at(int j) const { return col[j % 3] & row[j / 3]; }
+};
 
 // Workgroups go to the chip's 8 XCDs in turn (workgroup i to XCD i mod 8),
 // each XCD with an L2 of its own.  This maps launch index i to a work item
