@@ -539,7 +539,7 @@ __global__ void __launch_bounds__(256) k_sort_lists(ViewTable vt, StatePtrs st, 
 }
 
 // Lists longer than a wave sorts, one workgroup per list: workgroup b takes
-// the long lists among kLongChunk tiles, whose counts its threads read at
+// the long lists among `chunk` tiles, whose counts its threads read at
 // once (no queue, no global atomic).  Tile i of the launch is tile
 // i (2^31 - 1) mod n, a permutation (2^31 - 1 is a prime above n) that
 // spreads the long lists, which cluster in neighbouring tiles and at the
@@ -552,20 +552,167 @@ __global__ void __launch_bounds__(256) k_sort_lists(ViewTable vt, StatePtrs st, 
 // both runs (keys of the first run go before equal keys of the second).  In
 // place: every thread merges its outputs into registers first and all write
 // after a barrier, so the block needs one buffer (18 KB); the last level's
-// outputs go to the list at once.  Longer lists (rare; a correctness path):
-// the bitonic network on global memory.
-constexpr int kLongChunk = 16;
+// outputs go to the list at once.
+// Longer lists, up to kRankRuns such buffers: each kSortLds keys sorted so in
+// place, then a key's position is its index in its own run plus the number of
+// smaller keys in each of the others (keys are unique), found by binary search
+// in LDS, eight keys of a thread at a time, about 6 us per pair of runs.  Beyond
+// that (a correctness path) a bitonic network in global memory, whose steps
+// each wait for memory but whose work grows less than quadratically: at 30
+// runs it is the faster one (3.9 against 5.3 ms for the scene below).
+// What bounds it is the latency of one list: 90 -> 27 us for 8000 patches in a
+// 1000x1000 view with tiles of 16, 72 -> 22 us for three views near 701x523, both
+// by one list per workgroup instead of several; 16 -> 3.9 ms with 334 lists
+// beyond the buffer (2880 patches' lattice Gaussians, 14 views of 144x144).
+constexpr int kLongChunk = 16;  // the most tiles per workgroup
+constexpr int kRankRuns = 16;
+constexpr int kLongGroups = 2560;  // see launch_binning
 static_assert(kSortLds == 4 * kWaveSort, "the four waves of a workgroup sort one run each");
 
-__global__ void __launch_bounds__(256) k_sort_long(ViewTable vt, StatePtrs st, int lat_per_view) {
+// Sorts src[0, cnt), cnt <= kSortLds, by a workgroup of 256 threads;
+// out(i, key) takes the i-th smallest.  Every key is read before the first
+// call of out.
+template <typename Out>
+__device__ __forceinline__ void block_sort(const unsigned long long *src, int cnt, unsigned long long *keys, Out &&out) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    // runs of 512 keys, one wave each: loaded into the buffer in 64-lane
+    // runs (a thread's loads all in flight), read by each lane as 8
+    // consecutive keys, sorted in registers
+    {
+        unsigned long long x[kSortLds / 256];
+#pragma unroll
+        for (int r = 0; r < kSortLds / 256; ++r) {
+            const int i = r * 256 + (int)threadIdx.x;
+            x[r] = i < cnt ? src[i] : 0ull;
+        }
+#pragma unroll
+        for (int r = 0; r < kSortLds / 256; ++r) {
+            const int i = r * 256 + (int)threadIdx.x;
+            if (i < cnt) keys[stage_slot(i)] = x[r];
+        }
+    }
+    __syncthreads();
+    if (wave * kWaveSort < cnt) {
+        unsigned long long x[8];
+        const int b0 = wave * kWaveSort + lane * 8;
+#pragma unroll
+        for (int r = 0; r < 8; ++r) x[r] = b0 + r < cnt ? keys[stage_slot(b0 + r)] : ~0ull;
+        wave_sort_regs<8>(x, lane);
+#pragma unroll
+        for (int r = 0; r < 8; ++r)
+            if (b0 + r < cnt) keys[stage_slot(b0 + r)] = x[r];
+    }
+    __syncthreads();
+    if (cnt <= kWaveSort)  // (the end of a longer list: one run, nothing to merge)
+        for (int i = threadIdx.x; i < cnt; i += blockDim.x) out(i, keys[stage_slot(i)]);
+    // outputs per thread: a power of two, so that no thread's outputs
+    // straddle two pairs of runs
+    int per = 1;
+    while (per * 256 < cnt) per <<= 1;
+    for (int L = kWaveSort; L < cnt; L <<= 1) {
+        unsigned long long x[kSortLds / 256];
+        const int d0 = threadIdx.x * per;
+        int m = 0;
+        if (d0 < cnt) {
+            const int p0 = d0 & ~(2 * L - 1);
+            const int mid = min(p0 + L, cnt), end = min(p0 + 2 * L, cnt);
+            const int la = mid - p0, lb = end - mid, d = d0 - p0;
+            // how many of the pair's first d outputs come from the first
+            // run (the first run's keys go before equal keys of the second)
+            int lo = max(0, d - lb), hi = min(d, la);
+            while (lo < hi) {
+                const int c = (lo + hi) >> 1;
+                if (keys[stage_slot(p0 + c)] <= keys[stage_slot(mid + d - 1 - c)]) lo = c + 1;
+                else hi = c;
+            }
+            int i = lo, j = d - lo;
+            // (reads one past a run's end stay in the buffer, which has a
+            // slot past the last key; their values are never taken)
+            unsigned long long ka = keys[stage_slot(p0 + i)], kb = keys[stage_slot(mid + j)];
+            m = min(per, end - d0);
+#pragma unroll
+            for (int k = 0; k < kSortLds / 256; ++k)
+                if (k < m) {
+                    const bool take_a = i < la && (j >= lb || ka <= kb);
+                    x[k] = take_a ? ka : kb;
+                    i += take_a;
+                    j += !take_a;
+                    const unsigned long long nx = keys[stage_slot(take_a ? p0 + i : mid + j)];
+                    ka = take_a ? nx : ka;
+                    kb = take_a ? kb : nx;
+                }
+        }
+        if (2 * L >= cnt) {  // the last level
+#pragma unroll
+            for (int k = 0; k < kSortLds / 256; ++k)
+                if (k < m) out(d0 + k, x[k]);
+        } else {  // in place: all read, then all write
+            __syncthreads();
+#pragma unroll
+            for (int k = 0; k < kSortLds / 256; ++k)
+                if (k < m) keys[stage_slot(d0 + k)] = x[k];
+            __syncthreads();
+        }
+    }
+    __syncthreads();  // the next use of the buffer
+}
+
+// Positions of the keys of the runs src[kSortLds r, kSortLds (r + 1)), each
+// sorted, in the order of all of them: out(i, key).
+template <typename Out>
+__device__ __forceinline__ void block_rank_runs(const unsigned long long *src, int cnt, unsigned long long *keys,
+                                                Out &&out) {
+    constexpr int R = kSortLds / 256;
+    auto load = [&](int b0, unsigned long long *y) {  // (a thread's loads all in flight)
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const int i = b0 + r * 256 + (int)threadIdx.x;
+            y[r] = i < cnt ? src[i] : ~0ull;
+        }
+    };
+    for (int a0 = 0; a0 < cnt; a0 += kSortLds) {
+        const int na = min(kSortLds, cnt - a0);
+        unsigned long long x[R], y[R];
+        int rank[R];
+        load(a0, x);
+#pragma unroll
+        for (int r = 0; r < R; ++r) rank[r] = r * 256 + (int)threadIdx.x;
+        int b0 = a0 == 0 ? kSortLds : 0;
+        load(b0, y);
+        while (b0 < cnt) {
+            const int nb = min(kSortLds, cnt - b0);
+#pragma unroll
+            for (int r = 0; r < R; ++r) keys[stage_slot(r * 256 + (int)threadIdx.x)] = y[r];
+            __syncthreads();
+            b0 += b0 + kSortLds == a0 ? 2 * kSortLds : kSortLds;
+            load(b0, y);  // (the next run is on its way during the search)
+            int pos[R];
+#pragma unroll
+            for (int r = 0; r < R; ++r) pos[r] = 0;
+            for (int step = kSortLds; step > 0; step >>= 1)
+#pragma unroll
+                for (int r = 0; r < R; ++r) {
+                    const int q = min(pos[r] + step, kSortLds);
+                    pos[r] = pos[r] + step <= nb && keys[stage_slot(q - 1)] < x[r] ? q : pos[r];
+                }
+#pragma unroll
+            for (int r = 0; r < R; ++r) rank[r] += pos[r];
+            __syncthreads();
+        }
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+            if (r * 256 + (int)threadIdx.x < na) out(rank[r], x[r]);
+    }
+}
+
+__global__ void __launch_bounds__(256, 5) k_sort_long(ViewTable vt, StatePtrs st, int lat_per_view, int chunk) {
     __shared__ unsigned long long keys[kSortLds + kSortLds / 8 + 1];
     __shared__ int long_tiles[kLongChunk], n_long;
     const int which = blockIdx.y;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     if (threadIdx.x == 0) n_long = 0;
     __syncthreads();
-    if (threadIdx.x < kLongChunk) {
-        const int i = blockIdx.x * kLongChunk + threadIdx.x;
+    if ((int)threadIdx.x < chunk) {
+        const int i = blockIdx.x * chunk + threadIdx.x;
         if (i < vt.total_tiles) {
             const int t = (int)((int64_t)i * 2147483647ll % vt.total_tiles);
             if ((which == 0 ? st.g_count[t] : st.b_count[t]) > kWaveSort) long_tiles[atomicAdd(&n_long, 1)] = t;
@@ -585,8 +732,16 @@ __global__ void __launch_bounds__(256) k_sort_long(ViewTable vt, StatePtrs st, i
             dst[i] = (uint32_t)rec;
             if (gpos) gpos[rec] = start + i;
         };
-        if (cnt > kSortLds) {
-            if (threadIdx.x == 0) atomicAdd((unsigned long long *)&st.counters[C_BIGSORT], 1ull);
+        if (cnt <= kSortLds) {
+            block_sort(src, cnt, keys, emit);
+            continue;
+        }
+        if (threadIdx.x == 0) atomicAdd((unsigned long long *)&st.counters[C_BIGSORT], 1ull);
+        if (cnt <= kRankRuns * kSortLds) {
+            for (int r = 0; r < cnt; r += kSortLds)
+                block_sort(src + r, min(kSortLds, cnt - r), keys, [&](int i, unsigned long long key) { src[r + i] = key; });
+            block_rank_runs(src, cnt, keys, emit);
+        } else {
             int n2 = 1;
             while (n2 < cnt) n2 <<= 1;
             bitonic_steps<NoGet>(n2, [&](int a, int b) {
@@ -595,74 +750,8 @@ __global__ void __launch_bounds__(256) k_sort_long(ViewTable vt, StatePtrs st, i
                 if (y < x) { src[a] = y; src[b] = x; }
             });
             for (int i = threadIdx.x; i < cnt; i += blockDim.x) emit(i, src[i]);
-            __syncthreads();
-            continue;
-        }
-        // runs of 512 keys, one wave each: loaded into the buffer in 64-lane
-        // runs, read by each lane as 8 consecutive keys, sorted in registers
-        for (int i = threadIdx.x; i < cnt; i += blockDim.x) keys[stage_slot(i)] = src[i];
-        __syncthreads();
-        if (wave * kWaveSort < cnt) {
-            unsigned long long x[8];
-            const int b0 = wave * kWaveSort + lane * 8;
-#pragma unroll
-            for (int r = 0; r < 8; ++r) x[r] = b0 + r < cnt ? keys[stage_slot(b0 + r)] : ~0ull;
-            wave_sort_regs<8>(x, lane);
-#pragma unroll
-            for (int r = 0; r < 8; ++r)
-                if (b0 + r < cnt) keys[stage_slot(b0 + r)] = x[r];
         }
         __syncthreads();
-        // outputs per thread: a power of two, so that no thread's outputs
-        // straddle two pairs of runs
-        int per = 1;
-        while (per * 256 < cnt) per <<= 1;
-        for (int L = kWaveSort; L < cnt; L <<= 1) {
-            unsigned long long x[kSortLds / 256];
-            const int d0 = threadIdx.x * per;
-            int m = 0;
-            if (d0 < cnt) {
-                const int p0 = d0 & ~(2 * L - 1);
-                const int mid = min(p0 + L, cnt), end = min(p0 + 2 * L, cnt);
-                const int la = mid - p0, lb = end - mid, d = d0 - p0;
-                // how many of the pair's first d outputs come from the first
-                // run (the first run's keys go before equal keys of the second)
-                int lo = max(0, d - lb), hi = min(d, la);
-                while (lo < hi) {
-                    const int c = (lo + hi) >> 1;
-                    if (keys[stage_slot(p0 + c)] <= keys[stage_slot(mid + d - 1 - c)]) lo = c + 1;
-                    else hi = c;
-                }
-                int i = lo, j = d - lo;
-                // (reads one past a run's end stay in the buffer, which has a
-                // slot past the last key; their values are never taken)
-                unsigned long long ka = keys[stage_slot(p0 + i)], kb = keys[stage_slot(mid + j)];
-                m = min(per, end - d0);
-#pragma unroll
-                for (int k = 0; k < kSortLds / 256; ++k)
-                    if (k < m) {
-                        const bool take_a = i < la && (j >= lb || ka <= kb);
-                        x[k] = take_a ? ka : kb;
-                        i += take_a;
-                        j += !take_a;
-                        const unsigned long long nx = keys[stage_slot(take_a ? p0 + i : mid + j)];
-                        ka = take_a ? nx : ka;
-                        kb = take_a ? kb : nx;
-                    }
-            }
-            if (2 * L >= cnt) {  // the last level: its outputs are the list
-#pragma unroll
-                for (int k = 0; k < kSortLds / 256; ++k)
-                    if (k < m) emit(d0 + k, x[k]);
-            } else {  // in place: all read, then all write
-                __syncthreads();
-#pragma unroll
-                for (int k = 0; k < kSortLds / 256; ++k)
-                    if (k < m) keys[stage_slot(d0 + k)] = x[k];
-                __syncthreads();
-            }
-        }
-        __syncthreads();  // the next list reuses the buffer
     }
 }
 
@@ -699,8 +788,14 @@ hipError_t launch_binning(const Consts &k, const ViewTable &vt, const StatePtrs 
     }
     hipLaunchKernelGGL(k_sort_lists, dim3((unsigned)((2 * (int64_t)n + 3) / 4)), dim3(256), 0, s, vt, st,
                        lat_per_view);
-    hipLaunchKernelGGL(k_sort_long, dim3((unsigned)((n + kLongChunk - 1) / kLongChunk), 2), dim3(256), 0, s, vt, st,
-                       lat_per_view);
+    // Tiles per workgroup of the long lists: one, so that no workgroup sorts
+    // several lists one after the other, up to kLongGroups tiles (twice as many
+    // workgroups, what the chip holds at once); beyond, more tiles, since nearly
+    // all of the workgroups would only find that they have no long list
+    int chunk = 1;
+    while (chunk < kLongChunk && n / chunk > kLongGroups) chunk <<= 1;
+    hipLaunchKernelGGL(k_sort_long, dim3((unsigned)((n + chunk - 1) / chunk), 2), dim3(256), 0, s, vt, st,
+                       lat_per_view, chunk);
     return hipGetLastError();
 }
 
