@@ -3,6 +3,8 @@ photometric loss of Eq. 9 (bgt_loss) and the Adam update (bgt_adam_step).
 PyTorch only holds the device memory and supplies the stream."""
 from __future__ import annotations
 
+import gc
+
 import numpy as np
 import torch
 
@@ -126,6 +128,9 @@ class TrainStep:
     def _capture(self):
         self()  # warm-up outside the capture (first launches load the kernels)
         torch.cuda.synchronize()
+        # a renderer left in a reference cycle frees its pinned memory when the
+        # collector finds it, which during the capture would invalidate that
+        gc.collect()
         g = torch.cuda.CUDAGraph()
         with torch.cuda.graph(g):
             self()
