@@ -41,7 +41,7 @@ struct Shape {
     int64_t N, NT;
     int64_t NR;  // Gaussian records: the N pixel records, then the lattice Gaussians of every view
     int64_t off[BGT_STATE_FIELDS];
-    int64_t wverts_off, patch_off, gsum_off;
+    int64_t patch_off, gsum_off;
 };
 
 bgt_status fail(bgt_ctx *ctx, bgt_status st, const char *msg) {
@@ -154,10 +154,8 @@ bgt_status make_shape(bgt_ctx *ctx, const bgt_prims *pr, const bgt_views *vw, Sh
     put(F_LAST, 4 * N);
     {
         const int64_t vbytes = (int64_t)sizeof(VertRec) * vt.n * k.VL * k.P;
-        const int64_t wbytes = 24 * (int64_t)k.VL * k.P;
         sh.off[F_VERTS] = o;
-        sh.wverts_off = align256(o + vbytes);
-        sh.patch_off = align256(sh.wverts_off + wbytes);
+        sh.patch_off = align256(o + vbytes);
         sh.gsum_off = align256(sh.patch_off + 4 * (int64_t)k.pdw * k.P);
         o = align256(sh.gsum_off + 4 * (int64_t)k.gdw * k.P);
     }
@@ -199,7 +197,6 @@ StatePtrs state_ptrs(const Shape &sh, void *state) {
     p.T_final = (float *)(b + sh.off[F_TFINAL]);
     p.last = (int32_t *)(b + sh.off[F_LAST]);
     p.verts = (VertRec *)(b + sh.off[F_VERTS]);
-    p.wverts = (double *)(b + sh.wverts_off);
     p.patch = (float *)(b + sh.patch_off);
     p.gsum = (float *)(b + sh.gsum_off);
     p.g_count = (int32_t *)(b + sh.off[F_GCOUNT]);
@@ -407,7 +404,7 @@ bgt_status bgt_tessellate(bgt_ctx *ctx, const bgt_prims *prims, float *verts, vo
     k.degree = prims->degree;
     k.ncp = (prims->degree + 1) * (prims->degree + 2) / 2;
     k.P = prims->num_prims;
-    hipError_t e = launch_tessellate(k, prim_ptrs(prims), nullptr, verts, (hipStream_t)stream);
+    hipError_t e = launch_tessellate(k, prim_ptrs(prims), verts, (hipStream_t)stream);
     if (e != hipSuccess) return hip_fail(ctx, e, "tessellate");
     return BGT_OK;
 }
@@ -444,17 +441,15 @@ bgt_status bgt_render_fwd(bgt_ctx *ctx, const bgt_prims *prims, const bgt_views 
     const StatePtrs sp = state_ptrs(sh, state);
     const PrimPtrs pp = prim_ptrs(prims);
     hipError_t e;
-    {  // counters, z-buffer and tile counts start at zero
-        ZeroTable z;
+    {
+        StageTimer tm(ctx, 0, st);
+        ZeroTable z;  // counters, z-buffer and tile counts start at zero
         z.add(sp.counters, 2 * (int64_t)kCounterWords);
         z.add(sp.zbuf, 2 * (int64_t)sh.N);
         z.add(sp.g_count, sh.NT);
         z.add(sp.b_count, sh.NT);
-        if ((e = launch_zero(z, st)) != hipSuccess) return hip_fail(ctx, e, "clear");
-    }
-    {
-        StageTimer tm(ctx, 0, st);
-        if ((e = launch_raster(sh.k, sh.vt, pp, views->cams, sp, st)) != hipSuccess) return hip_fail(ctx, e, "raster");
+        if ((e = launch_front(sh.k, sh.vt, pp, views->cams, sp, z, st)) != hipSuccess) return hip_fail(ctx, e, "front");
+        if ((e = launch_raster(sh.k, sh.vt, sp, st)) != hipSuccess) return hip_fail(ctx, e, "raster");
     }
     {
         StageTimer tm(ctx, 1, st);
@@ -462,14 +457,12 @@ bgt_status bgt_render_fwd(bgt_ctx *ctx, const bgt_prims *prims, const bgt_views 
     }
     {
         StageTimer tm(ctx, 2, st);
-        if ((e = launch_binning(sh.k, sh.vt, sp, st)) != hipSuccess) return hip_fail(ctx, e, "binning");
+        if ((e = launch_binning(sh.k, sh.vt, sp, ctx->ovf_dev, st)) != hipSuccess) return hip_fail(ctx, e, "binning");
     }
     {
         StageTimer tm(ctx, 3, st);
         if ((e = launch_blend_fwd(sh.k, sh.vt, sp, images, st)) != hipSuccess) return hip_fail(ctx, e, "blend_fwd");
     }
-    if (ctx->ovf_dev && (e = launch_note_overflow(sp, ctx->ovf_dev, st)) != hipSuccess)
-        return hip_fail(ctx, e, "overflow note");
     return BGT_OK;
 }
 

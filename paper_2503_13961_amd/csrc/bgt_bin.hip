@@ -80,6 +80,44 @@ __global__ void __launch_bounds__(1024) k_scan_top(int64_t *sums, int nb, int64_
     }
 }
 
+// The segments of a thread's kScanItems consecutive tiles from `base`, whose
+// first starts at `off`: starts, cursors, and counts cut at the capacity.
+// Returns whether any was cut.
+__device__ __forceinline__ bool scan_write(int32_t *cnt, int32_t *st, int32_t *cur, int base, int n, int64_t off,
+                                           const int32_t *v, int64_t cap) {
+    bool ovf = false;
+    int32_t c4[kScanItems], s4[kScanItems];
+#pragma unroll
+    for (int i = 0; i < kScanItems; ++i) {
+        int64_t c = v[i];
+        if (off + c > cap) { c = off < cap ? cap - off : 0; ovf |= base + i < n; }
+        s4[i] = (int32_t)(off < cap ? off : cap);
+        c4[i] = (int32_t)c;
+        off += v[i];
+    }
+    static_assert(kScanItems == 4, "one 16-byte store each");
+    if (base + kScanItems <= n) {  // (base is a multiple of 4, the arrays start on 256 bytes)
+        *(int4 *)(st + base) = *(int4 *)(cur + base) = make_int4(s4[0], s4[1], s4[2], s4[3]);
+        if (ovf) *(int4 *)(cnt + base) = make_int4(c4[0], c4[1], c4[2], c4[3]);
+    } else {
+#pragma unroll
+        for (int i = 0; i < kScanItems; ++i)
+            if (base + i < n) { st[base + i] = cur[base + i] = s4[i]; cnt[base + i] = c4[i]; }
+    }
+    return ovf;
+}
+
+// a thread's kScanItems consecutive counts from `base` (0 past the end)
+__device__ __forceinline__ void scan_read(const int32_t *cnt, int base, int n, int32_t *v) {
+    if (base + kScanItems <= n) {
+        const int4 q = *(const int4 *)(cnt + base);
+        v[0] = q.x; v[1] = q.y; v[2] = q.z; v[3] = q.w;
+    } else {
+#pragma unroll
+        for (int i = 0; i < kScanItems; ++i) v[i] = base + i < n ? cnt[base + i] : 0;
+    }
+}
+
 __global__ void __launch_bounds__(kScanThreads) k_scan_down(int32_t *gc, int32_t *gs, int32_t *gcur, int32_t *bc,
                                                             int32_t *bs, int32_t *bcur, const int64_t *sums,
                                                             int n, int nb, int64_t cap_g, int64_t cap_b,
@@ -88,32 +126,47 @@ __global__ void __launch_bounds__(kScanThreads) k_scan_down(int32_t *gc, int32_t
     const int base = blockIdx.x * kScanBlock + threadIdx.x * kScanItems;
     for (int which = 0; which < 2; ++which) {
         int32_t *cnt = which == 0 ? gc : bc;
-        int32_t *st = which == 0 ? gs : bs;
-        int32_t *cur = which == 0 ? gcur : bcur;
-        const int64_t cap = which == 0 ? cap_g : cap_b;
-        int64_t v[kScanItems], s = 0;
+        int32_t v[kScanItems];
+        scan_read(cnt, base, n, v);
+        int64_t s = 0, tot;
 #pragma unroll
-        for (int i = 0; i < kScanItems; ++i) {
-            v[i] = base + i < n ? cnt[base + i] : 0;
-            s += v[i];
-        }
-        int64_t tot;
-        int64_t off = block_exclusive_scan<int64_t>(s, tot, ws) + sums[(int64_t)which * nb + blockIdx.x];
-        bool ovf = false;
-#pragma unroll
-        for (int i = 0; i < kScanItems; ++i) {
-            if (base + i < n) {
-                int64_t c = v[i];
-                if (off + c > cap) { c = off < cap ? cap - off : 0; ovf = true; }
-                const int64_t sclamp = off < cap ? off : cap;
-                st[base + i] = (int32_t)sclamp;
-                cur[base + i] = (int32_t)sclamp;
-                cnt[base + i] = (int32_t)c;
-            }
-            off += v[i];
-        }
-        if (ovf) atomicOr((unsigned long long *)&counters[C_OVERFLOW], which == 0 ? 1ull : 2ull);
+        for (int i = 0; i < kScanItems; ++i) s += v[i];
+        const int64_t off = block_exclusive_scan<int64_t>(s, tot, ws) + sums[(int64_t)which * nb + blockIdx.x];
+        if (scan_write(cnt, which == 0 ? gs : bs, which == 0 ? gcur : bcur, base, n, off, v, which == 0 ? cap_g : cap_b))
+            atomicOr((unsigned long long *)&counters[C_OVERFLOW], which == 0 ? 1ull : 2ull);
     }
+}
+
+// The whole scan in one launch, a workgroup of 1024 threads per list kind, for
+// up to kScanOne tiles: all counts are loaded at once, four per thread in each
+// of four rounds of 4096 tiles, whose scans then follow each other.  10000
+// tiles: 7 us, where the other path's three launches take 14 and two gaps.
+constexpr int kScanRounds = 4, kScanOne = 1024 * kScanItems * kScanRounds;
+
+__global__ void __launch_bounds__(1024) k_scan_one(int32_t *gc, int32_t *gs, int32_t *gcur, int32_t *bc, int32_t *bs,
+                                                   int32_t *bcur, int n, int64_t cap_g, int64_t cap_b,
+                                                   int64_t *counters) {
+    __shared__ int64_t ws[33];
+    const bool g = blockIdx.x == 0;
+    int32_t *cnt = g ? gc : bc;
+    int32_t v[kScanRounds][kScanItems];
+#pragma unroll
+    for (int r = 0; r < kScanRounds; ++r) scan_read(cnt, (r * 1024 + threadIdx.x) * kScanItems, n, v[r]);
+    int64_t carry = 0;
+    bool ovf = false;
+#pragma unroll
+    for (int r = 0; r < kScanRounds; ++r) {
+        if (r * 1024 * kScanItems >= n) break;
+        int64_t s = 0, tot;
+#pragma unroll
+        for (int i = 0; i < kScanItems; ++i) s += v[r][i];
+        const int64_t off = block_exclusive_scan<int64_t>(s, tot, ws) + carry;
+        ovf |= scan_write(cnt, g ? gs : bs, g ? gcur : bcur, (r * 1024 + threadIdx.x) * kScanItems, n, off, v[r],
+                          g ? cap_g : cap_b);
+        carry += tot;
+    }
+    if (ovf) atomicOr((unsigned long long *)&counters[C_OVERFLOW], g ? 1ull : 2ull);
+    if (threadIdx.x == 0) counters[g ? C_GPAIRS : C_BPAIRS] = carry;
 }
 
 // ------------------------------------------------------------ scatter
@@ -509,9 +562,19 @@ __device__ __forceinline__ void wave_sort_split(const unsigned long long *src, i
 
 // One wave per list: list L < n_tiles is the Gaussian list of tile L, the
 // others the boundary lists.  Empty lists cost a wave a few instructions.
-__global__ void __launch_bounds__(256) k_sort_lists(ViewTable vt, StatePtrs st, int lat_per_view) {
+// The first thread also copies the pass's overflow bits (complete since the
+// scan), when there are any, into the context's word of pinned host memory: a
+// later call on the context (and bgt_query) reads it without waiting for the
+// device.  A plain system-scope store, not an atomic, so nothing depends on the
+// host bridge's atomics.
+__global__ void __launch_bounds__(256) k_sort_lists(ViewTable vt, StatePtrs st, int lat_per_view,
+                                                    unsigned long long *flag) {
     __shared__ unsigned long long stage[4][kStageKeys];
     const int lane = threadIdx.x & 63;
+    if (blockIdx.x == 0 && threadIdx.x == 0 && flag) {
+        const unsigned long long f = (unsigned long long)st.counters[C_OVERFLOW];
+        if (f) __hip_atomic_store(flag, f, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    }
     const int L = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
     if (L >= 2 * vt.total_tiles) return;
     const int which = L < vt.total_tiles ? 0 : 1, t = which == 0 ? L : L - vt.total_tiles;
@@ -755,31 +818,22 @@ __global__ void __launch_bounds__(256, 5) k_sort_long(ViewTable vt, StatePtrs st
     }
 }
 
-// Copies the pass's overflow bits, when there are any, into the context's
-// word of pinned host memory: a later call on the context (and bgt_query)
-// reads it without waiting for the device.  A plain system-scope store, not
-// an atomic, so nothing depends on the host bridge's atomics.
-__global__ void k_note_overflow(const int64_t *counters, unsigned long long *flag) {
-    if (threadIdx.x != 0) return;
-    const unsigned long long f = (unsigned long long)counters[C_OVERFLOW];
-    if (f) __hip_atomic_store(flag, f, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-}
-
-hipError_t launch_note_overflow(const StatePtrs &st, unsigned long long *flag, hipStream_t s) {
-    hipLaunchKernelGGL(k_note_overflow, dim3(1), dim3(64), 0, s, (const int64_t *)st.counters, flag);
-    return hipGetLastError();
-}
-
-hipError_t launch_binning(const Consts &k, const ViewTable &vt, const StatePtrs &st, hipStream_t s) {
+hipError_t launch_binning(const Consts &k, const ViewTable &vt, const StatePtrs &st, unsigned long long *flag,
+                          hipStream_t s) {
     const int n = vt.total_tiles;
-    const int nb = (n + kScanBlock - 1) / kScanBlock;
-    int64_t *sums = (int64_t *)st.scan_tmp;
-    hipLaunchKernelGGL(k_scan_reduce, dim3(nb), dim3(kScanThreads), 0, s, (const int32_t *)st.g_count,
-                       (const int32_t *)st.b_count, n, sums, nb);
-    hipLaunchKernelGGL(k_scan_top, dim3(1), dim3(1024), 0, s, sums, nb, st.counters);
-    hipLaunchKernelGGL(k_scan_down, dim3(nb), dim3(kScanThreads), 0, s, st.g_count, st.g_start, st.g_cursor,
-                       st.b_count, st.b_start, st.b_cursor, (const int64_t *)sums, n, nb, k.cap_g, k.cap_b,
-                       st.counters);
+    if (n <= kScanOne) {
+        hipLaunchKernelGGL(k_scan_one, dim3(2), dim3(1024), 0, s, st.g_count, st.g_start, st.g_cursor, st.b_count,
+                           st.b_start, st.b_cursor, n, k.cap_g, k.cap_b, st.counters);
+    } else {
+        const int nb = (n + kScanBlock - 1) / kScanBlock;
+        int64_t *sums = (int64_t *)st.scan_tmp;
+        hipLaunchKernelGGL(k_scan_reduce, dim3(nb), dim3(kScanThreads), 0, s, (const int32_t *)st.g_count,
+                           (const int32_t *)st.b_count, n, sums, nb);
+        hipLaunchKernelGGL(k_scan_top, dim3(1), dim3(1024), 0, s, sums, nb, st.counters);
+        hipLaunchKernelGGL(k_scan_down, dim3(nb), dim3(kScanThreads), 0, s, st.g_count, st.g_start, st.g_cursor,
+                           st.b_count, st.b_start, st.b_cursor, (const int64_t *)sums, n, nb, k.cap_g, k.cap_b,
+                           st.counters);
+    }
     hipLaunchKernelGGL(k_scatter, dim3((unsigned)((vt.total_b8 + 3) / 4)), dim3(256), 0, s, k, vt, st);
     const int lat_per_view = k.P * k.NL;
     if (lat_per_view > 0) {
@@ -787,7 +841,7 @@ hipError_t launch_binning(const Consts &k, const ViewTable &vt, const StatePtrs 
         hipLaunchKernelGGL(k_scatter_lattice, dim3((unsigned)((nl + 255) / 256)), dim3(256), 0, s, k, vt, st);
     }
     hipLaunchKernelGGL(k_sort_lists, dim3((unsigned)((2 * (int64_t)n + 3) / 4)), dim3(256), 0, s, vt, st,
-                       lat_per_view);
+                       lat_per_view, flag);
     // Tiles per workgroup of the long lists: one, so that no workgroup sorts
     // several lists one after the other, up to kLongGroups tiles (twice as many
     // workgroups, what the chip holds at once); beyond, more tiles, since nearly

@@ -7,6 +7,8 @@
 // Every quantity that decides an integer (snapped coordinates, coverage,
 // depth order, tile ranges) is computed in FP64.  The blending stages read
 // FP32 copies.
+#include <algorithm>
+
 #include "bgt_internal.h"
 #include "bgt_sh.h"
 
@@ -17,9 +19,9 @@ namespace bgt {
 // Clears the table's segments laid end to end in 16-byte chunks, each
 // segment's chunks starting at its own base: one store per chunk, or word by
 // word for a segment's last chunk and for a base that is not 16-byte aligned.
-__global__ void k_zero(ZeroTable t, int64_t total_chunks) {
-    for (int64_t c = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; c < total_chunks;
-         c += (int64_t)gridDim.x * blockDim.x) {
+// Chunks c, c + step, ... of total_chunks.
+__device__ __forceinline__ void zero_chunks(const ZeroTable &t, int64_t c, int64_t step, int64_t total_chunks) {
+    for (; c < total_chunks; c += step) {
         int s = 0;
         int64_t first = 0;  // first chunk of segment s
         while (s + 1 < t.n && c >= first + ((t.words[s] + 3) >> 2)) {
@@ -36,17 +38,25 @@ __global__ void k_zero(ZeroTable t, int64_t total_chunks) {
     }
 }
 
-hipError_t launch_zero(const ZeroTable &t, hipStream_t s) {
-    int64_t chunks = 0;
-    for (int i = 0; i < t.n; ++i) chunks += (t.words[i] + 3) >> 2;
-    if (chunks == 0) return hipSuccess;
-    int64_t b = (chunks + 255) / 256;
-    if (b > 4096) b = 4096;
-    hipLaunchKernelGGL(k_zero, dim3((unsigned)b), dim3(256), 0, s, t, chunks);
-    return hipGetLastError();
+__global__ void k_zero(ZeroTable t, int64_t total_chunks) {
+    zero_chunks(t, blockIdx.x * (int64_t)blockDim.x + threadIdx.x, (int64_t)gridDim.x * blockDim.x, total_chunks);
 }
 
-// ------------------------------------------------------------ Bernstein basis
+static int64_t zero_total(const ZeroTable &t) {
+    int64_t chunks = 0;
+    for (int i = 0; i < t.n; ++i) chunks += (t.words[i] + 3) >> 2;
+    return chunks;
+}
+
+// workgroups of 256 threads that clear that many chunks
+static unsigned zero_blocks(int64_t chunks) { return (unsigned)std::min<int64_t>((chunks + 255) / 256, 4096); }
+
+hipError_t launch_zero(const ZeroTable &t, hipStream_t s) {
+    const int64_t chunks = zero_total(t);
+    if (chunks == 0) return hipSuccess;
+    hipLaunchKernelGGL(k_zero, dim3(zero_blocks(chunks)), dim3(256), 0, s, t, chunks);
+    return hipGetLastError();
+}
 
 // n!/(i! j! k!) u^i v^j w^k in the order of Eq. 1's double sum.
 template <int DEG, typename T>
@@ -116,38 +126,41 @@ __device__ __forceinline__ void subtri_corners_ab(int L, int s, int *m, int *ca,
     for (int c = 0; c < 3; ++c) m[c] = lattice_index(L, ca[c], cb[c]);
 }
 
+// Eq. 1-2 at lattice node m of patch p.
 template <int DEG>
-__global__ void k_tessellate(Consts k, PrimPtrs pr, double *wverts, float *verts_out) {
+__device__ __forceinline__ void lattice_point(const Consts &k, const float *ctrl, int m, int p, double *S) {
     constexpr int NCP = (DEG + 1) * (DEG + 2) / 2;
-    int64_t idx = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (idx >= (int64_t)k.VL * k.P) return;
-    const int p = (int)(idx % k.P), m = (int)(idx / k.P);
     int a, b;
     lattice_node(k.L, m, a, b);
     const double u = (double)a / k.L, v = (double)b / k.L, w = (double)(k.L - a - b) / k.L;
     double B[NCP];
     bernstein<DEG>(u, v, w, B);
-    double S[3] = {0.0, 0.0, 0.0};
+    S[0] = S[1] = S[2] = 0.0;
 #pragma unroll
     for (int c = 0; c < NCP; ++c)
 #pragma unroll
-        for (int d = 0; d < 3; ++d) S[d] += B[c] * (double)pr.ctrl[((int64_t)d * NCP + c) * k.P + p];
-    if (wverts)
-        for (int d = 0; d < 3; ++d) wverts[((int64_t)m * k.P + p) * 3 + d] = S[d];
-    if (verts_out)
-        for (int d = 0; d < 3; ++d) verts_out[((int64_t)d * k.VL + m) * k.P + p] = (float)S[d];
+        for (int d = 0; d < 3; ++d) S[d] += B[c] * (double)ctrl[((int64_t)d * NCP + c) * k.P + p];
 }
 
-hipError_t launch_tessellate(const Consts &k, const PrimPtrs &pr, double *wverts, float *verts_out,
-                             hipStream_t s) {
+template <int DEG>
+__global__ void k_tessellate(Consts k, const float *ctrl, float *verts) {
+    const int64_t idx = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+    if (idx >= (int64_t)k.VL * k.P) return;
+    const int p = (int)(idx % k.P), m = (int)(idx / k.P);
+    double S[3];
+    lattice_point<DEG>(k, ctrl, m, p, S);
+    for (int d = 0; d < 3; ++d) verts[((int64_t)d * k.VL + m) * k.P + p] = (float)S[d];
+}
+
+hipError_t launch_tessellate(const Consts &k, const PrimPtrs &pr, float *verts, hipStream_t s) {
     int64_t n = (int64_t)k.VL * k.P;
     dim3 grid((unsigned)((n + 255) / 256)), block(256);
     switch (k.degree) {
-        case 1: hipLaunchKernelGGL(k_tessellate<1>, grid, block, 0, s, k, pr, wverts, verts_out); break;
-        case 2: hipLaunchKernelGGL(k_tessellate<2>, grid, block, 0, s, k, pr, wverts, verts_out); break;
-        case 3: hipLaunchKernelGGL(k_tessellate<3>, grid, block, 0, s, k, pr, wverts, verts_out); break;
-        case 4: hipLaunchKernelGGL(k_tessellate<4>, grid, block, 0, s, k, pr, wverts, verts_out); break;
-        case 5: hipLaunchKernelGGL(k_tessellate<5>, grid, block, 0, s, k, pr, wverts, verts_out); break;
+        case 1: hipLaunchKernelGGL(k_tessellate<1>, grid, block, 0, s, k, pr.ctrl, verts); break;
+        case 2: hipLaunchKernelGGL(k_tessellate<2>, grid, block, 0, s, k, pr.ctrl, verts); break;
+        case 3: hipLaunchKernelGGL(k_tessellate<3>, grid, block, 0, s, k, pr.ctrl, verts); break;
+        case 4: hipLaunchKernelGGL(k_tessellate<4>, grid, block, 0, s, k, pr.ctrl, verts); break;
+        case 5: hipLaunchKernelGGL(k_tessellate<5>, grid, block, 0, s, k, pr.ctrl, verts); break;
         default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
@@ -159,12 +172,11 @@ hipError_t launch_tessellate(const Consts &k, const PrimPtrs &pr, double *wverts
 // the opacity copied as they are, and Eq. 5 with a resolution-1 attribute
 // map, one rotation and scale per patch: R(q/|q|) diag(exp(log_scale)) and
 // r_b^2 = (r_ref / sharpness)^2 in FP64.
-__global__ void k_prim_setup(Consts k, PrimPtrs pr, float *patch) {
-    // one thread per word of a patch record, the patch index fastest (the
-    // parameter arrays are read in runs of consecutive patches); the thread
-    // of M's first word computes the rotation-scale setup and writes all 20
-    // of its words
-    const int64_t idx = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+// One thread (index idx) per word of a patch record, the patch index fastest
+// (the parameter arrays are read in runs of consecutive patches); the thread
+// of M's first word computes the rotation-scale setup and writes all 20 of its
+// words.
+__device__ __forceinline__ void prim_setup(const Consts &k, const PrimPtrs &pr, float *patch, int64_t idx) {
     if (idx >= (int64_t)k.P * k.pdw) return;
     const int p = (int)(idx % k.P), i = (int)(idx / k.P);
     const int ncp = k.ncp, mo = patch_m_off(ncp), qo = patch_q_off(ncp);
@@ -241,14 +253,10 @@ __device__ __forceinline__ void cam_apply(const Cam &c, const double *X, double 
     for (int r = 0; r < 3; ++r) t[r] = c.R[3 * r] * X[0] + c.R[3 * r + 1] * X[1] + c.R[3 * r + 2] * X[2] + c.t[r];
 }
 
-__global__ void k_project(Consts k, ViewTable vt, const float *cams, const double *wverts, VertRec *verts) {
-    int64_t idx = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    const int64_t per_view = (int64_t)k.VL * k.P;
-    if (idx >= per_view * vt.n) return;
-    const int v = (int)(idx / per_view);
-    const int64_t mp = idx % per_view;
-    const Cam c = load_cam(cams, v);
-    double X[3] = {wverts[mp * 3], wverts[mp * 3 + 1], wverts[mp * 3 + 2]}, t[3];
+// Projection and snapping of the lattice point X in a view (X == INT32_MIN
+// where it is not in front of the near plane, or too far off).
+__device__ __forceinline__ VertRec project(const Consts &k, const Cam &c, const double *X) {
+    double t[3];
     cam_apply(c, X, t);
     VertRec r;
     r.x = r.y = r.iz = 0.0;
@@ -266,7 +274,57 @@ __global__ void k_project(Consts k, ViewTable vt, const float *cams, const doubl
             r.Y = (int32_t)rint(y * 256.0);
         }
     }
-    verts[idx] = r;
+    return r;
+}
+
+// What a pass needs before its raster, in one launch of three kinds of
+// workgroups: the first zb clear the pass's counters and z-buffer, the next pb
+// write the patch records, the others tessellate a lattice point and project
+// it into `views_per` views each.  Launches of a few microseconds, each
+// followed by a gap of 2, bound the single view: one 800x800 view 14 -> 7 us
+// and three gaps fewer; large launches move the same bytes (50000 patches, 32
+// views: 265 -> 242 us).
+template <int DEG>
+__global__ void __launch_bounds__(256) k_front(Consts k, ViewTable vt, PrimPtrs pr, const float *cams, ZeroTable z,
+                                               int64_t zero_n, int zb, int pb, int views_per, float *patch,
+                                               VertRec *verts) {
+    const int bid = blockIdx.x;
+    if (bid < zb) {
+        zero_chunks(z, bid * (int64_t)256 + threadIdx.x, (int64_t)zb * 256, zero_n);
+    } else if (bid < zb + pb) {
+        prim_setup(k, pr, patch, (bid - zb) * (int64_t)256 + threadIdx.x);
+    } else {
+        const int64_t per_view = (int64_t)k.VL * k.P;
+        const int64_t i = (bid - zb - pb) * (int64_t)256 + threadIdx.x;
+        const int v0 = (int)(i / per_view) * views_per;
+        if (v0 >= vt.n) return;
+        const int64_t mp = i % per_view;
+        double X[3];
+        lattice_point<DEG>(k, pr.ctrl, (int)(mp / k.P), (int)(mp % k.P), X);
+        for (int v = v0; v < min(v0 + views_per, vt.n); ++v) verts[v * per_view + mp] = project(k, load_cam(cams, v), X);
+    }
+}
+
+hipError_t launch_front(const Consts &k, const ViewTable &vt, const PrimPtrs &pr, const float *cams,
+                        const StatePtrs &st, const ZeroTable &z, hipStream_t s) {
+    const int64_t chunks = zero_total(z), per_view = (int64_t)k.VL * k.P;
+    const unsigned zb = zero_blocks(chunks), pb = (unsigned)(((int64_t)k.P * k.pdw + 255) / 256);
+    // a point's evaluation is shared by four views where that leaves the chip
+    // full (2^20 threads)
+    const int views_per = per_view * vt.n >= ((int64_t)1 << 22) ? 4 : 1;
+    const int64_t n = per_view * ((vt.n + views_per - 1) / views_per);
+    dim3 grid(zb + pb + (unsigned)((n + 255) / 256)), block(256);
+#define BGT_FRONT(D)                                                                                               \
+    case D:                                                                                                        \
+        hipLaunchKernelGGL(k_front<D>, grid, block, 0, s, k, vt, pr, cams, z, chunks, (int)zb, (int)pb, views_per, \
+                           st.patch, st.verts);                                                                    \
+        break;
+    switch (k.degree) {
+        BGT_FRONT(1) BGT_FRONT(2) BGT_FRONT(3) BGT_FRONT(4) BGT_FRONT(5)
+        default: return hipErrorInvalidValue;
+    }
+#undef BGT_FRONT
+    return hipGetLastError();
 }
 
 // ------------------------------------------------------------ raster
@@ -1012,15 +1070,7 @@ __global__ void __launch_bounds__(256) k_gen_lattice(Consts k, ViewTable vt, con
     });
 }
 
-hipError_t launch_raster(const Consts &k, const ViewTable &vt, const PrimPtrs &pr, const float *cams,
-                         const StatePtrs &st, hipStream_t s) {
-    hipError_t e;
-    if ((e = launch_tessellate(k, pr, st.wverts, nullptr, s)) != hipSuccess) return e;
-    {
-        const int64_t n = (int64_t)vt.n * k.VL * k.P;
-        hipLaunchKernelGGL(k_project, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, k, vt, cams,
-                           (const double *)st.wverts, st.verts);
-    }
+hipError_t launch_raster(const Consts &k, const ViewTable &vt, const StatePtrs &st, hipStream_t s) {
     {
         const int64_t n = ((int64_t)vt.n * k.L2 * k.P + 7) / 8 * 8;  // (whole groups of 8)
         // triangles per wave: 64 where that leaves the 1024 SIMDs four waves
@@ -1038,8 +1088,6 @@ hipError_t launch_raster(const Consts &k, const ViewTable &vt, const PrimPtrs &p
 
 hipError_t launch_gen(const Consts &k, const ViewTable &vt, const PrimPtrs &pr, const float *cams,
                       const StatePtrs &st, hipStream_t s) {
-    hipLaunchKernelGGL(k_prim_setup, dim3((unsigned)(((int64_t)k.P * k.pdw + 255) / 256)), dim3(256), 0, s, k, pr,
-                       st.patch);
     const bool ext = k.T > 1 || k.K > 0;  // resolution-3 maps or SH colour
     {
         dim3 grid((unsigned)((vt.total_b8 + 3) / 4)), block(256);  // one wave per 8x8 block

@@ -174,7 +174,7 @@ struct GradPtrs {
     float *ctrl, *color, *log_scale, *quat, *opacity, *sharp, *sh;
 };
 
-// Packed per-patch record in dwords, written by k_prim_setup so that the
+// Packed per-patch record in dwords, written by prim_setup so that the
 // generation pass reads a patch with a few scalar loads:
 //   [0, 3 NCP)      control points, [c][d]
 //   [3 NCP, 6 NCP)  colour control points, [c][d]
@@ -236,7 +236,6 @@ struct StatePtrs {
     float *T_final;
     int32_t *last;
     VertRec *verts;        // [V][VL][P]
-    double *wverts;        // [VL][P][3] world lattice
     float *patch;          // [P][patch_dw(ncp)] packed per-patch record (see patch_dw)
     float *gsum;           // [P][gdw] gradient sums of the backward (zeroed by each backward)
     int32_t *g_count, *g_start, *g_cursor;
@@ -323,14 +322,16 @@ struct DensifyRule {
 
 // ---------------------------------------------------------------- launchers
 
-hipError_t launch_tessellate(const Consts &k, const PrimPtrs &pr, double *wverts, float *verts_out,
-                             hipStream_t s);
-hipError_t launch_raster(const Consts &k, const ViewTable &vt, const PrimPtrs &pr, const float *cams,
-                         const StatePtrs &st, hipStream_t s);
+hipError_t launch_tessellate(const Consts &k, const PrimPtrs &pr, float *verts, hipStream_t s);
+struct ZeroTable;
+hipError_t launch_front(const Consts &k, const ViewTable &vt, const PrimPtrs &pr, const float *cams,
+                        const StatePtrs &st, const ZeroTable &z, hipStream_t s);
+hipError_t launch_raster(const Consts &k, const ViewTable &vt, const StatePtrs &st, hipStream_t s);
 hipError_t launch_gen(const Consts &k, const ViewTable &vt, const PrimPtrs &pr, const float *cams,
                       const StatePtrs &st, hipStream_t s);
-hipError_t launch_binning(const Consts &k, const ViewTable &vt, const StatePtrs &st, hipStream_t s);
-hipError_t launch_note_overflow(const StatePtrs &st, unsigned long long *flag, hipStream_t s);
+// flag: the context's overflow word in pinned host memory, or null
+hipError_t launch_binning(const Consts &k, const ViewTable &vt, const StatePtrs &st, unsigned long long *flag,
+                          hipStream_t s);
 
 // context internals for the entry points outside bgt_api.cpp
 int ctx_device(const bgt_ctx *ctx);
