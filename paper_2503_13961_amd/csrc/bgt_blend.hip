@@ -23,14 +23,14 @@
 
 namespace bgt {
 
-// Per-wave gamma* rows in LDS (forward, backward; the backward keeps a row of
-// dl/dgamma* sums beside each), boundary points staged at once and entries of
-// the run table.  Rows beyond those go to memory the binning has left unused
+// Per-wave rows of w (Eq. 6) in LDS (forward, backward; the backward sums dl/dw
+// of each in registers), boundary points staged at once and entries of the run
+// table.  Rows beyond those go to memory the binning has left unused
 // (RowPool), a longer list is staged in chunks, and only primitives beyond the
 // run table, or rows the pool has no room for, are searched per pixel and
 // Gaussian.  The budget sets how many waves share a SIMD: at 8 px (one wave
-// per workgroup) under 6.25 KB with 32-entry batches; `batch` 64 takes the variant with more points
-// and rows for scenes with more runs per tile.  The 2000-patch sphere at
+// per workgroup) under 6.25 KB with 32-entry batches; `batch` 64 takes the
+// variant with more points and rows for scenes with more runs per tile.  The 2000-patch sphere at
 // 16 x 800^2 has at most 12 runs and 91 points in an 8 px tile (mean 2.6
 // runs); in the 50,000-patch sphere at 32 x 1024x768 a third of the tiles have
 // more than 12 runs (up to 33) and up to 120 points.  LDS is allocated in units
@@ -43,7 +43,17 @@ namespace bgt {
 template <int TS, int K>
 struct BlendDims {
     static constexpr int NW = TS * TS / 64;                          // waves
-    static constexpr int KI = TS == 8 ? 32 : K;                      // Gaussians staged per batch
+    // Gaussians staged per batch of a wave: every wave stages the tile's list
+    // for its own 8x8 block, whichever the tile size, and goes through it at its
+    // own pace.  (The waves of a 16 or 32 px tile shared batches staged by
+    // one of them, with two barriers each, at which they waited for the
+    // slowest: forward of 2000 patches' lattice in 8 views of 800x800 0.96 ->
+    // 0.77 ms, 8000 cubic patches at 1000x1000 0.245 -> 0.19 ms; 32 px tiles,
+    // four views of 800x800, 1.34 -> 0.57 ms.)  64 entries fill the loaders'
+    // lanes (16 px, 32 entries: 0.80 ms for the lattice), 32 keep a fifth
+    // wave per SIMD at 8 px and in the backward.
+    static constexpr int KI_FWD = TS == 8 ? 32 : 64;
+    static constexpr int KI_BWD = 32;
     static constexpr int CAP = TS >= 32 ? 512 : (TS >= 16 ? 256 : (K > 32 ? 112 : 88));
     static constexpr int NR = TS >= 16 ? 128 : (K > 32 ? 96 : 64);
     static constexpr int RM_FWD = TS >= 16 ? 12 : (K > 32 ? 12 : 8);
@@ -119,44 +129,20 @@ __device__ __forceinline__ bool in_mask(LaneMask m) { return __builtin_amdgcn_in
 __device__ __forceinline__ bool any_lane(bool b) { return lanes(b) != 0ull; }
 __device__ __forceinline__ bool all_lanes(bool b) { return !any_lane(!b); }
 
-// A staged Gaussian's mean is kept per wave as (g - w0) + delta, where g is
-// the Gaussian's own pixel, w0 the origin of the wave's 8x8 block and delta
+// A wave's batch.  A staged Gaussian's mean is kept as (g - w0) + delta, where
+// g is the Gaussian's own pixel, w0 the origin of the wave's 8x8 block and delta
 // the mean's offset from g's centre: one rounding that does not depend on
 // the tile size.
-template <int TS, int K>
+template <int KI>
 struct BatchLds {
-    using D = BlendDims<TS, K>;
-    static constexpr int KI = D::KI, NW = D::NW;
-    // per-wave mean offsets and (primitive id, row): at 8 px (one wave) side
-    // by side in 16-byte records like e and c, so that one address serves
-    // every per-entry read; otherwise every wave has its own row of the run
-    static constexpr bool PACK = TS == 8;
     struct MP {
         float2 m;
-        int2 pr;
+        int2 pr;  // primitive, row code: a row index, kNoRow (the run has no point near the block: gamma* = 1) or kSearch
     };
-    struct Packed {
-        MP mp[KI];
-    };
-    struct Apart {
-        float2 m[NW][KI];
-        int prim[KI];
-        int8_t row[NW][KI];
-        int xr[KI], yr[KI];
-    };
-    typename std::conditional<PACK, Packed, Apart>::type v;
+    // (three 16-byte records: one address serves every read of an entry)
+    MP mp[KI];
     float4 e[KI];  // conic in exponent form kE (a, 2b, c), opacity
-    float4 c[KI];  // colour; w: exponent below which no pixel of a 4x4 sub-block is in the support
-    __device__ __forceinline__ float2 m(int w, int kk) const {
-        if constexpr (PACK) return v.mp[kk].m;
-        else return v.m[w][kk];
-    }
-    // (primitive, row code) of entry kk for wave w: a row index, kNoRow (the
-    // run has no point near the block: gamma* = 1) or kSearch
-    __device__ __forceinline__ int2 pr(int w, int kk) const {
-        if constexpr (PACK) return v.mp[kk].pr;
-        else return make_int2(v.prim[kk], (int)v.row[w][kk]);
-    }
+    float4 c[KI];  // colour; w: free (the backward's record index)
 };
 constexpr int kNoRow = -1, kSearch = -2;
 
@@ -578,44 +564,40 @@ __device__ __forceinline__ float sub_block_bound(float qa, float qb, float qc, f
     return kE * rad * rad;
 }
 
-// Stages a loaded record as batch entry kk.  At 8 px returns the entry's
-// sub_blocks (the loaders are the wave that uses them); larger tiles take them
-// from the staged entry, each wave for its own block.
-template <int TS, int K, typename BL>
-__device__ __forceinline__ int stage_slot(BatchLds<TS, K> &S, const SlotPrefetch &P, int kk, int ox, int oy, const BL &B,
-                                          const RowInfo &R, float kappa) {
-    using G = TileGeom<TS>;
-    // tile-relative pixel the Gaussian's mean is stored against
+// Stages a loaded record as entry kk of the batch of wave `wave`, whose block
+// starts at (wx0, wy0); returns the entry's sub_blocks.
+template <int KI, typename BL>
+__device__ __forceinline__ int stage_slot(BatchLds<KI> &S, const SlotPrefetch &P, int kk, int wx0, int wy0, const BL &B,
+                                          const RowInfo &R, float kappa, int wave) {
+    // the pixel the Gaussian's mean is stored against
     const int a = __float_as_int(P.r2.w);
-    const int x = lo16(a) - ox, y = hi16(a) - oy;
+    const int x = lo16(a) - wx0, y = hi16(a) - wy0;
     const float4 ex = make_float4(kE * P.r0.z, 2.0f * kE * P.r0.w, kE * P.r1.x, P.r2.x);
     const float thr = sub_block_bound(P.r0.z, P.r0.w, P.r1.x, kappa);
     S.e[kk] = ex;
-    S.c[kk] = make_float4(P.r1.y, P.r1.z, P.r1.w, thr);
-    const int g = __float_as_int(P.r2.y), xr = __float_as_int(P.r3.x), yr = __float_as_int(P.r3.y);
+    S.c[kk] = make_float4(P.r1.y, P.r1.z, P.r1.w, 0.0f);
+    const int g = __float_as_int(P.r2.y);
     const int r = find_run(B.run_prim, R.n_runs, g);
-    const int absent = R.many && g > B.run_prim[BL::NR - 1] ? kSearch : kNoRow;
-    if constexpr (G::NT == 64) {
-        const float2 m = make_float2((float)x + P.r0.x, (float)y + P.r0.y);
-        S.v.mp[kk].m = m;
-        S.v.mp[kk].pr = make_int2(g, r < 0 ? absent : (r < R.nrow ? r : kSearch));
-        return sub_blocks(m, ex, thr, xr, yr, ox, oy);
-    } else {
-#pragma unroll
-        for (int w = 0; w < G::NT / 64; ++w) {
-            S.v.m[w][kk] = make_float2((float)(x - (w % G::SPR) * 8) + P.r0.x, (float)(y - (w / G::SPR) * 8) + P.r0.y);
-            int row = absent;
-            if (r >= 0) {
-                row = (int)B.row_of[w][r];
-                row = row == 255 ? kNoRow : (row < B.nmap[w] ? row : kSearch);
-            }
-            S.v.row[w][kk] = (int8_t)row;
+    int row = R.many && g > B.run_prim[BL::NR - 1] ? kSearch : kNoRow;
+    if (r >= 0) {
+        if constexpr (BL::NW == 1) {
+            row = r < R.nrow ? r : kSearch;
+        } else {
+            row = (int)B.row_of[wave][r];
+            row = row == 255 ? kNoRow : (row < B.nmap[wave] ? row : kSearch);
         }
-        S.v.prim[kk] = g;
-        S.v.xr[kk] = xr;
-        S.v.yr[kk] = yr;
-        return 0;
     }
+    const float2 m = make_float2((float)x + P.r0.x, (float)y + P.r0.y);
+    S.mp[kk].m = m;
+    S.mp[kk].pr = make_int2(g, row);
+    return sub_blocks(m, ex, thr, __float_as_int(P.r3.x), __float_as_int(P.r3.y), wx0, wy0);
+}
+
+// Between a wave's writes and reads of its own batch (its LDS accesses
+// complete in order: the fence keeps the compiler from moving them across each other).
+__device__ __forceinline__ void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+    __builtin_amdgcn_wave_barrier();
 }
 
 // ------------------------------------------------------------ forward
@@ -625,10 +607,11 @@ __global__ void __launch_bounds__(TS *TS) k_blend_fwd(Consts k, ViewTable vt, St
     using G = TileGeom<TS>;
     using D = BlendDims<TS, K>;
     using BL = BoundaryLds<TS, K, D::RM_FWD>;
-    constexpr int RM = BL::RM, NW = D::NW, KI = D::KI;
+    constexpr int RM = BL::RM, NW = D::NW, KI = D::KI_FWD;
     __shared__ BL B;
-    __shared__ BatchLds<TS, K> S;
-    const int t = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    __shared__ BatchLds<KI> SB[NW];
+    const int t = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = NW > 1 ? __builtin_amdgcn_readfirstlane(tid >> 6) : 0;
+    BatchLds<KI> &S = SB[wave];
     const int v = view_of_tile(vt, t);
     const ViewInfo vi = vt.v[v];
     const int tl = t - vi.tile_off, tx = tl % vi.tiles_x, ty = tl / vi.tiles_x;
@@ -663,8 +646,8 @@ __global__ void __launch_bounds__(TS *TS) k_blend_fwd(Consts k, ViewTable vt, St
     // staged, so that the two waits overlap
     const int gs0 = st.g_start[t], gc = st.g_count[t];
     SlotPrefetch pf;
-    pf.gp_next = (tid < KI && tid < gc) ? (int)st.g_list[gs0 + tid] : -1;
-    pf.issue(st, gs0, gc, 0, tid, KI);
+    pf.gp_next = (lane < KI && lane < gc) ? (int)st.g_list[gs0 + lane] : -1;
+    pf.issue(st, gs0, gc, 0, lane, KI);
     const RowInfo R = build_rows<TS, K, false>(B, st, pool, bs0, bc, ox, oy, lx, ly, h);
     if (R.n_runs > RM && tid == 0) atomicAdd((unsigned long long *)&st.counters[C_MANYRUNS], 1ull);
     const float *const map = &B.map[wave * RM][lane];
@@ -678,92 +661,77 @@ __global__ void __launch_bounds__(TS *TS) k_blend_fwd(Consts k, ViewTable vt, St
     // support test d^T Q d <= 2 ln(1/g_min) as a base-2 exponent: G = 2^e, e >= log2(g_min)
     const float e_min = kE * k.kappa2;
     const float kappa = sqrtf(k.kappa2);
-    unsigned staged = 0;  // (8 px) the staged batch's entries for this lane's row
-    {
+    unsigned long long staged = 0;  // the staged batch's entries for this lane's row
+    auto stage = [&] {
         int bits = 0;
-        if (pf.gp >= 0) bits = stage_slot<TS, K>(S, pf, tid, ox, oy, B, R, kappa);
-        if constexpr (NW == 1) staged = (unsigned)row_mask(bits, lane);
-    }
+        if (pf.gp >= 0) bits = stage_slot(S, pf, lane, wx0, wy0, B, R, kappa, wave);
+        staged = row_mask(bits, lane);
+    };
+    stage();
     for (int base = 0; base < gc; base += KI) {
-        if constexpr (NW == 1) {
-            __syncthreads();  // publishes the staged batch
-            if (all_lanes(done)) break;
-        } else {
-            if (__syncthreads_and(done ? 1 : 0)) break;  // also publishes the staged batch
-        }
+        wave_sync();
+        if (all_lanes(done)) break;
         int stop_kk = -1;  // batch index of the entry at which this pixel stops in this batch
-        pf.issue(st, gs0, gc, base + KI, tid, KI);   // next batch's records, in flight during compositing
-        const int nk = min(KI, gc - base);
-        if (!all_lanes(done)) {
-            for (int c0 = 0; c0 < nk; c0 += 64) {
-                unsigned long long mine = staged;
-                if constexpr (NW > 1) {
-                    const int j = c0 + lane, jj = j < KI ? j : KI - 1;
-                    const int bits = sub_blocks(S.m(wave, jj), S.e[jj], S.c[jj].w, S.v.xr[jj], S.v.yr[jj], wx0, wy0);
-                    mine = row_mask(j < nk ? bits : 0, lane);
-                }
-                if (row_all(done, lane)) mine = 0;  // this row has stopped
+        pf.issue(st, gs0, gc, base + KI, lane, KI);   // next batch's records, in flight during compositing
+        unsigned long long mine = staged;
+        if (row_all(done, lane)) mine = 0;  // this row has stopped
 #pragma unroll
-                for (int hb = 0; hb < (KI > 32 ? 64 : 32); hb += 32) {
-                    unsigned mm = (unsigned)(mine >> hb);
-                    if (any_lane(mm != 0u)) do {
-                        // each row composites its own next entry: branch-free per
-                        // lane, a lane that does not composite it takes alpha = 0,
-                        // which leaves T and C bit-identical
-                        const bool act = mm != 0u;
-                        const int kk = c0 + hb + low_bit(mm);
-                        mm &= mm - 1u;
-                        const int2 pr = S.pr(wave, kk);
-                        const float2 m = S.m(wave, kk);
-                        const float4 ex = S.e[kk];
-                        const float4 c = S.c[kk];
-                        const int g = pr.x, r = pr.y;  // uniform within the row
-                        const bool own = g == h || nob;  // w = 1 for all without coefficients
-                        const float dx = qx - m.x, dy = qy - m.y;
-                        const float e = fmaf(dx, fmaf(ex.x, dx, ex.y * dy), ex.z * dy * dy);
-                        // w = 0 without a boundary point of g near this block, or outside the support
-                        bool live = act && !done && (own || r != kNoRow) && e >= e_min;
-                        // (at 16 and 32 px a step in which no lane's support
-                        // is reached leaves before the weights; T and C would
-                        // not change)
-                        if (TS >= 16 && !any_lane(live)) continue;
-                        // w = 0 (gamma* = 1 for another patch's Gaussian) gives
-                        // a = 0 with no test: T and C stay as they are
-                        float w = map[min(max(r, 0), RM - 1) * 64];
-                        w = (unsigned)r < (unsigned)RM ? w : 1.0f;
-                        if (far && any_lane(live && (r >= RM || r == kSearch))) {
-                            if (live && r >= RM) {
-                                w = R.extra[(int64_t)(r - RM) * 64 + lane];
-                            } else if (live && r == kSearch) {
-                                float gam;
-                                search_prim(B, st, bs0, bc, g, R.n_runs, lx, ly, ox, oy, &gam);
-                                w = weight(gam, own);
-                            }
-                        }
-                        // min(raw, alpha_max) as integers: the same as fminf for
-                        // every non-NaN raw, alpha_max being positive (one
-                        // instruction; fminf also canonicalizes alpha_max)
-                        float a = __int_as_float(min(__float_as_int(ex.w * w * support_exp2(e)), __float_as_int(amax)));
-                        a = live ? a : 0.0f;
-                        const float ta = T * a;
-                        C0 += ta * c.x;
-                        C1 += ta * c.y;
-                        C2 += ta * c.z;
-                        T = T * (1.0f - a);
-                        // (the stopping entry's batch index; the list index is
-                        // formed once per batch below)
-                        const bool stop = live && T < tmin;
-                        done = done || stop;
-                        stop_kk = stop ? kk : stop_kk;
-                    } while (any_lane(mm != 0u));
+        for (int hb = 0; hb < (KI > 32 ? 64 : 32); hb += 32) {
+            unsigned mm = (unsigned)(mine >> hb);
+            if (any_lane(mm != 0u)) do {
+                // each row composites its own next entry: branch-free per
+                // lane, a lane that does not composite it takes alpha = 0,
+                // which leaves T and C bit-identical
+                const bool act = mm != 0u;
+                const int kk = hb + low_bit(mm);
+                mm &= mm - 1u;
+                const int2 pr = S.mp[kk].pr;
+                const float2 m = S.mp[kk].m;
+                const float4 ex = S.e[kk];
+                const float4 c = S.c[kk];
+                const int g = pr.x, r = pr.y;  // uniform within the row
+                const bool own = g == h || nob;  // w = 1 for all without coefficients
+                const float dx = qx - m.x, dy = qy - m.y;
+                const float e = fmaf(dx, fmaf(ex.x, dx, ex.y * dy), ex.z * dy * dy);
+                // w = 0 without a boundary point of g near this block, or outside the support
+                bool live = act && !done && (own || r != kNoRow) && e >= e_min;
+                // (at 16 and 32 px a step in which no lane's support
+                // is reached leaves before the weights; T and C would
+                // not change)
+                if (TS >= 16 && !any_lane(live)) continue;
+                // w = 0 (gamma* = 1 for another patch's Gaussian) gives
+                // a = 0 with no test: T and C stay as they are
+                float w = map[min(max(r, 0), RM - 1) * 64];
+                w = (unsigned)r < (unsigned)RM ? w : 1.0f;
+                if (far && any_lane(live && (r >= RM || r == kSearch))) {
+                    if (live && r >= RM) {
+                        w = R.extra[(int64_t)(r - RM) * 64 + lane];
+                    } else if (live && r == kSearch) {
+                        float gam;
+                        search_prim(B, st, bs0, bc, g, R.n_runs, lx, ly, ox, oy, &gam);
+                        w = weight(gam, own);
+                    }
                 }
-            }
+                // min(raw, alpha_max) as integers: the same as fminf for
+                // every non-NaN raw, alpha_max being positive (one
+                // instruction; fminf also canonicalizes alpha_max)
+                float a = __int_as_float(min(__float_as_int(ex.w * w * support_exp2(e)), __float_as_int(amax)));
+                a = live ? a : 0.0f;
+                const float ta = T * a;
+                C0 += ta * c.x;
+                C1 += ta * c.y;
+                C2 += ta * c.z;
+                T = T * (1.0f - a);
+                // (the stopping entry's batch index; the list index is
+                // formed once per batch below)
+                const bool stop = live && T < tmin;
+                done = done || stop;
+                stop_kk = stop ? kk : stop_kk;
+            } while (any_lane(mm != 0u));
         }
         if (stop_kk >= 0) last = base + stop_kk + 1;
-        __syncthreads();  // everyone is done with this batch
-        int bits = 0;
-        if (pf.gp >= 0) bits = stage_slot<TS, K>(S, pf, tid, ox, oy, B, R, kappa);
-        if constexpr (NW == 1) staged = (unsigned)row_mask(bits, lane);
+        wave_sync();
+        stage();
     }
     if (inside) {
         image[3 * (int64_t)pix + 0] = C0 + T * k.bg[0];
@@ -873,7 +841,10 @@ __device__ __forceinline__ void route_boundary(const StatePtrs &st, int bpix, fl
 // the tile (plain stores: the parameter pass sums a record's slots over its
 // tiles in a fixed order, so the result does not depend on scheduling; a
 // record reaching more than 3 x 3 tiles adds into sums of its own by float
-// atomics instead); larger tiles add their waves' totals in LDS first.
+// atomics instead); larger tiles add their waves' totals in LDS first, in a
+// ring of batches, each stored by the last wave to finish it: with a barrier
+// per 64 entries the waves waited for the slowest a third of the time (four
+// views of 800x800, 16 px tiles: 0.92 -> 0.78 ms, 32 px 2.6 -> 2.2 ms).
 // The boundary terms accumulate per (row, pixel), as the sum of dl/dw, in
 // registers for the LDS rows (the row is wave-uniform), and go to the
 // minimising boundary point at the end.  16 views of 800x800, 2000 patches, 8 px
@@ -892,7 +863,7 @@ k_blend_bwd(Consts k, ViewTable vt, StatePtrs st, RowPool pool, const float *ima
     using G = TileGeom<TS>;
     using D = BlendDims<TS, K>;
     using BL = BoundaryLds<TS, K, D::RM_BWD>;
-    constexpr int RM = BL::RM, NW = D::NW, KI = D::KI, CAP = D::CAP;
+    constexpr int RM = BL::RM, NW = D::NW, KI = D::KI_BWD, CAP = D::CAP;
     constexpr bool ONE = NW == 1;
     __shared__ BL B;
     // sums of dl/dw per LDS row at this pixel (uniform index: indexed
@@ -904,9 +875,11 @@ k_blend_bwd(Consts k, ViewTable vt, StatePtrs st, RowPool pool, const float *ima
     for (int i = 0; i < RD; ++i) dgr[i] = 0.f;
     // the batch and its sums are dead once the list is done; the per-point
     // boundary sums reuse their space
+    // larger tiles: batches of the list whose sums the waves add up in LDS
+    constexpr int RING = ONE ? 1 : 4;
     struct LoopLds {
-        BatchLds<TS, K> S;
-        float acc[ONE ? 1 : KI * kSums];
+        BatchLds<KI> S[NW];
+        float acc[ONE ? 1 : RING * KI * kSums];
     };
     union TailLds {
         LoopLds loop;
@@ -914,11 +887,13 @@ k_blend_bwd(Consts k, ViewTable vt, StatePtrs st, RowPool pool, const float *ima
     };
     __shared__ TailLds U;
     __shared__ int max_last;
-    BatchLds<TS, K> &S = U.loop.S;
-    float *acc = U.loop.acc;
+    __shared__ int ring_done[RING], ring_free[RING];  // waves that finished a slot's batches; batches stored from it
+    float *acc = U.loop.acc;  // (the batch's first entry's sums)
     // runs of 64 neighbouring tiles per XCD: the sums of a record's tiles
     // then mostly meet in one L2
-    const int t = xcd_runs<64>(blockIdx.x, gridDim.x), tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int t = xcd_runs<64>(blockIdx.x, gridDim.x), tid = threadIdx.x, lane = tid & 63;
+    const int wave = NW > 1 ? __builtin_amdgcn_readfirstlane(tid >> 6) : 0;
+    BatchLds<KI> &S = U.loop.S[wave];
     const int gc = st.g_count[t];
     if (gc == 0) {  // no Gaussian reaches the tile: nothing to differentiate
         if (tid == 0) st.t_end[t] = 0;
@@ -959,15 +934,16 @@ k_blend_bwd(Consts k, ViewTable vt, StatePtrs st, RowPool pool, const float *ima
     // prefix, known once the stop indices are combined, are dropped then)
     const int gs0 = st.g_start[t];
     SlotPrefetch P;
-    P.load(st, (tid < KI && tid < gc) ? (int)st.g_list[gs0 + tid] : -1);
+    P.load(st, (lane < KI && lane < gc) ? (int)st.g_list[gs0 + lane] : -1);
     const int bs0 = st.b_start[t], bc = st.b_count[t];
     if constexpr (NW > 1) {
         if (tid == 0) max_last = 0;
+        if (tid < RING) ring_done[tid] = ring_free[tid] = 0;
         __syncthreads();
         if (lane == 0) atomicMax(&max_last, wave_last);
     }
     if constexpr (!ONE)
-        for (int i = tid; i < KI * kSums; i += TS * TS) acc[i] = 0.f;
+        for (int i = tid; i < RING * KI * kSums; i += TS * TS) acc[i] = 0.f;
     const RowInfo R = build_rows<TS, K, true>(B, st, pool, bs0, bc, ox, oy, lx, ly, h);  // (syncs)
     if constexpr (NW > 1) nlast = max_last;
     const float *const map = &B.map[wave * RM][lane];
@@ -999,7 +975,7 @@ k_blend_bwd(Consts k, ViewTable vt, StatePtrs st, RowPool pool, const float *ima
     // wave-uniform; -1: none left) and replays it at this lane's pixel if it is
     // one of the first `left` of the batch: leaves dl/do and T a.  SEARCH:
     // entries may need the per-pixel search
-    auto replay = [&](unsigned long long &mask, int c0, int left, float &d_o, float &ta, auto search) -> int {
+    auto replay = [&](unsigned long long &mask, int left, float &d_o, float &ta, auto search) -> int {
         constexpr bool SEARCH = decltype(search)::value;
         int kk = -1, g = 0, r = 0;
         float4 ex = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -1009,10 +985,10 @@ k_blend_bwd(Consts k, ViewTable vt, StatePtrs st, RowPool pool, const float *ima
         ta = 0.f;
         while (true) {
             if (!mask) return -1;
-            kk = c0 + __ffsll((long long)mask) - 1;
+            kk = __ffsll((long long)mask) - 1;
             mask &= mask - 1;
-            const int2 prk = S.pr(wave, kk);
-            const float2 m = S.m(wave, kk);
+            const int2 prk = S.mp[kk].pr;
+            const float2 m = S.mp[kk].m;
             ex = S.e[kk];
             g = prk.x;
             r = __builtin_amdgcn_readfirstlane(prk.y);
@@ -1073,7 +1049,7 @@ k_blend_bwd(Consts k, ViewTable vt, StatePtrs st, RowPool pool, const float *ima
         row_transpose(ta);
         const int j = lane >> 4;
         const int kj = j == 0 ? k0 : (j == 1 ? k1 : (j == 2 ? k2 : k3)), kq = max(kj, 0);
-        const float2 m = S.m(wave, kq);
+        const float2 m = S.mp[kq].m;
         const float o = S.e[kq].w;
         const float dx = bx - m.x, dy = by - m.y;
         const float sx = d[1] + d[3], sy = d[2] + d[3], s = sx + (d[0] + d[2]);
@@ -1111,89 +1087,108 @@ k_blend_bwd(Consts k, ViewTable vt, StatePtrs st, RowPool pool, const float *ima
         }
     };
 
-    int cur_gp = tid < nlast ? P.gp : -1;
-    bool wide = false;
-    unsigned staged = 0;  // (8 px) the staged batch's entries that reach the block
     constexpr int TSH = TS == 8 ? 3 : (TS == 16 ? 4 : 5);
-    auto stage = [&](int gp) {  // the record in P as this loader's entry; returns whether it is wide
-        const int bits = stage_slot<TS, K>(S, P, tid, ox, oy, B, R, kappa);
-        const bool wd = !narrow_range(__float_as_int(P.r3.x), __float_as_int(P.r3.y), TSH);
-        if constexpr (ONE) S.c[tid].w = __int_as_float(wd ? ~gp : gp);
-        return make_int2(bits, wd ? 1 : 0);
+    int cur_gp = lane < wave_last ? P.gp : -1;
+    bool wide = false;                    // this lane's entry adds to sums of its own
+    unsigned long long staged = 0;        // the staged batch's entries that reach the block
+    auto stage = [&](const SlotPrefetch &Q) {  // Q's record as this lane's entry of the batch; whether it reaches the block
+        wide = !narrow_range(__float_as_int(Q.r3.x), __float_as_int(Q.r3.y), TSH);
+        const int bits = stage_slot(S, Q, lane, wx0, wy0, B, R, kappa, wave);
+        if constexpr (ONE) S.c[lane].w = __int_as_float(wide ? ~Q.gp : Q.gp);
+        return bits != 0;
     };
     {
-        int2 b = make_int2(0, 0);
-        if (cur_gp >= 0) b = stage(cur_gp);
-        wide = b.y != 0;
-        if constexpr (ONE) staged = (unsigned)__ballot(b.x != 0);
+        bool reaches = false;
+        if (cur_gp >= 0) reaches = stage(P);
+        staged = __ballot(reaches);
     }
     for (int base = 0; base < nlast; base += KI) {
-        __syncthreads();  // publishes the staged batch
-        unsigned stored = 0u;                                          // (8 px) entries whose sums went to memory
-        const int left = mylast - base;                                // entries this lane replays
-        const int nkw = min(min(KI, nlast - base), wave_last - base);  // ... this wave
-        for (int c0 = 0; c0 < nkw; c0 += 64) {
-            unsigned long long mask = staged;
-            if constexpr (!ONE) {
-                const int j = c0 + lane, jj = j < KI ? j : KI - 1;
-                mask = __ballot(j < nkw &&
-                                sub_blocks(S.m(wave, jj), S.e[jj], S.c[jj].w, S.v.xr[jj], S.v.yr[jj], wx0, wy0) != 0);
+        wave_sync();
+        unsigned stored = 0u;            // (8 px) entries whose sums went to memory
+        const int left = mylast - base;  // entries this lane replays
+        unsigned long long mask = staged;
+        const int slot = base / KI % RING, gen = base / KI / RING;  // (larger tiles)
+        if constexpr (!ONE) {
+            // the slot's last batch has been stored
+            acc = U.loop.acc + slot * KI * kSums;
+            while (__hip_atomic_load(&ring_free[slot], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) < gen)
+                __builtin_amdgcn_s_sleep(1);
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+        }
+        if (R.search) {  // (rare) one entry at a time
+            while (mask) {
+                float d[4] = {0.f, 0.f, 0.f, 0.f}, ta[4] = {0.f, 0.f, 0.f, 0.f};
+                const int kk = replay(mask, left, d[0], ta[0], std::true_type());
+                if (kk < 0) break;
+                if constexpr (ONE) stored |= 1u << kk;
+                add_sums(kk, -1, -1, -1, d, ta);
             }
-            if (R.search) {  // (rare) one entry at a time
-                while (mask) {
-                    float d[4] = {0.f, 0.f, 0.f, 0.f}, ta[4] = {0.f, 0.f, 0.f, 0.f};
-                    const int kk = replay(mask, c0, left, d[0], ta[0], std::true_type());
-                    if (kk < 0) break;
-                    if constexpr (ONE) stored |= 1u << kk;
-                    add_sums(kk, -1, -1, -1, d, ta);
-                }
-            } else {
-                while (mask) {
-                    float d[4], ta[4];
-                    int ks[4];
+        } else {
+            while (mask) {
+                float d[4], ta[4];
+                int ks[4];
 #pragma unroll
-                    for (int s = 0; s < 4; ++s) {
-                        ks[s] = replay(mask, c0, left, d[s], ta[s], std::false_type());
-                        if constexpr (ONE) stored |= ks[s] >= 0 ? 1u << ks[s] : 0u;
-                    }
-                    if (ks[0] < 0) break;
-                    add_sums(ks[0], ks[1], ks[2], ks[3], d, ta);
+                for (int s = 0; s < 4; ++s) {
+                    ks[s] = replay(mask, left, d[s], ta[s], std::false_type());
+                    if constexpr (ONE) stored |= ks[s] >= 0 ? 1u << ks[s] : 0u;
                 }
+                if (ks[0] < 0) break;
+                add_sums(ks[0], ks[1], ks[2], ks[3], d, ta);
             }
         }
-        __syncthreads();
+        wave_sync();
         // the next batch is staged before this batch's sums are stored: a
-        // load issued after the stores would wait for them too (acc is not
-        // part of the stage)
-        const int next_gp = (tid < KI && base + KI + tid < nlast) ? (int)st.g_list[gs0 + base + KI + tid] : -1;
-        int2 b = make_int2(0, 0);
-        if (next_gp >= 0) {
-            P.load(st, next_gp);
-            b = stage(next_gp);
+        // load issued after the stores would wait for them too
+        const int prev_gp = cur_gp;
+        const bool prev_wide = wide;
+        cur_gp = lane < KI && base + KI + lane < wave_last ? (int)st.g_list[gs0 + base + KI + lane] : -1;
+        bool reaches = false;
+        if (cur_gp >= 0) {
+            SlotPrefetch Q;
+            Q.load(st, cur_gp);
+            reaches = stage(Q);
         }
-        if constexpr (ONE) staged = (unsigned)__ballot(b.x != 0);
-        if (tid < KI && cur_gp >= 0) {  // each loader stores its own entry's sums
-            if constexpr (ONE) {
-                // zero sums for the entries that do not reach the block
-                if (!wide && !((stored >> tid) & 1u)) zero_sums(gs_tile + (int64_t)cur_gp * kSums);
-            } else {
-                float *a = acc + tid * kSums;
-                if (wide) {
-                    float *dst = st.gwide + (int64_t)cur_gp * kSums;
-#pragma unroll
-                    for (int f = 0; f < kSums; ++f)
-                        if (a[f] != 0.f) unsafeAtomicAdd(&dst[f], a[f]);
-                } else {
-                    float *dst = gs_tile + (int64_t)cur_gp * kSums;
-#pragma unroll
-                    for (int f = 0; f < kSums; ++f) dst[f] = a[f];
+        staged = __ballot(reaches);
+        if constexpr (ONE) {
+            // zero sums for the entries that do not reach the block
+            if (lane < KI && prev_gp >= 0 && !prev_wide && !((stored >> lane) & 1u))
+                zero_sums(gs_tile + (int64_t)prev_gp * kSums);
+        } else {
+            // the last wave to finish a batch stores and clears its sums.  A
+            // wave may be up to RING batches ahead of the slowest: its wait
+            // above is for a batch that every wave is past, or storing, so the
+            // slowest never waits for another
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+            int before = 0;
+            if (lane == 0) before = __hip_atomic_fetch_add(&ring_done[slot], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            if (__builtin_amdgcn_readfirstlane(before) == NW * (gen + 1) - 1) {
+                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+                int gp = prev_gp;
+                bool wd = prev_wide;
+                if (gp < 0 && lane < KI && base + lane < nlast) {  // (past the last entry this wave replays)
+                    gp = (int)st.g_list[gs0 + base + lane];
+                    const int2 range = *(const int2 *)(st.rec + (int64_t)gp * 4 + 3);
+                    wd = !narrow_range(range.x, range.y, TSH);
                 }
+                if (gp >= 0) {
+                    float *a = acc + lane * kSums;
+                    if (wd) {
+                        float *dst = st.gwide + (int64_t)gp * kSums;
 #pragma unroll
-                for (int f = 0; f < kSums; ++f) a[f] = 0.f;
+                        for (int f = 0; f < kSums; ++f)
+                            if (a[f] != 0.f) unsafeAtomicAdd(&dst[f], a[f]);
+                    } else {
+                        float *dst = gs_tile + (int64_t)gp * kSums;
+#pragma unroll
+                        for (int f = 0; f < kSums; ++f) dst[f] = a[f];
+                    }
+#pragma unroll
+                    for (int f = 0; f < kSums; ++f) a[f] = 0.f;
+                }
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+                if (lane == 0) __hip_atomic_store(&ring_free[slot], gen + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
             }
         }
-        cur_gp = next_gp;
-        wide = b.y != 0;
     }
     // boundary points at the arg-min of each (run, pixel): d gamma / d b,
     // d sigma.  The arg-min is searched over the run (arg_min: the smallest
