@@ -41,7 +41,7 @@ struct Shape {
     int64_t N, NT;
     int64_t NR;  // Gaussian records: the N pixel records, then the lattice Gaussians of every view
     int64_t off[BGT_STATE_FIELDS];
-    int64_t patch_off, gsum_off;
+    int64_t patch_off, gsum_off, order_off;
 };
 
 bgt_status fail(bgt_ctx *ctx, bgt_status st, const char *msg) {
@@ -178,7 +178,8 @@ bgt_status make_shape(bgt_ctx *ctx, const bgt_prims *pr, const bgt_views *vw, Sh
     put(F_BIGTRI, 4 * k.cap_big);
     {
         sh.off[F_SCAN] = o;
-        o = align256(o + 16 * nb_scan);
+        sh.order_off = align256(o + 16 * nb_scan);
+        o = align256(sh.order_off + 4 * NT);
     }
     sh.off[F_END] = o;
     return BGT_OK;
@@ -218,6 +219,7 @@ StatePtrs state_ptrs(const Shape &sh, void *state) {
     p.brec64 = (double *)(b + sh.off[F_BREC64]);
     p.big_tris = (int32_t *)(b + sh.off[F_BIGTRI]);
     p.scan_tmp = (int32_t *)(b + sh.off[F_SCAN]);
+    p.order = (int32_t *)(b + sh.order_off);
     return p;
 }
 

@@ -49,23 +49,69 @@ __device__ __forceinline__ T block_exclusive_scan(T x, T &total, T *lds_waves) {
     return res;
 }
 
+// The blend passes take the tiles with the longest Gaussian lists first: a
+// tile's time is proportional to its list, and a long one that starts last
+// leaves the chip waiting for it; a view's few hundred long lists also spread
+// evenly over the SIMDs.  (Raster order before: backward of 2000 patches' lattice
+// in 8 views of 800x800 1.40 -> 1.21 ms; 8 px tiles, 16 views of 800x800
+// 1.80 -> 1.69 ms, forward 0.78 -> 0.75; one such view, forward, 106 -> 85 us.
+// The order costs 2 us in the scan, 7 at 393000 tiles.)  Classes are an eighth of an octave wide (in raster
+// order within one, roughly), the longest class 0, empty lists last.
+__device__ __forceinline__ int order_class(int len) {
+    if (len < 8) return kOrderClasses - 1 - len;
+    const int e = 31 - __clz(len);  // >= 3
+    return kOrderClasses - 1 - (8 * (e - 2) + ((len >> (e - 3)) & 7));
+}
+
+// Counts a tile with `len` entries (`in`: there is a tile) in the workgroup's
+// classes; returns its rank in its class.  A wave's empty tiles are counted
+// together.  Called by whole waves.
+__device__ __forceinline__ int order_count(int *classes, bool in, int len) {
+    const int lane = __lane_id();
+    const unsigned long long empty = __ballot(in && len == 0);
+    int first = 0;
+    if (empty && lane == __ffsll((long long)empty) - 1) first = atomicAdd(&classes[kOrderClasses - 1], __popcll(empty));
+    if (empty) first = __builtin_amdgcn_readlane(first, __ffsll((long long)empty) - 1);
+    int rank = first + __popcll(empty & ((1ull << lane) - 1ull));
+    if (in && len != 0) rank = atomicAdd(&classes[order_class(len)], 1);
+    return rank;
+}
+
 __global__ void __launch_bounds__(kScanThreads) k_scan_reduce(const int32_t *gc, const int32_t *bc, int n,
-                                                              int64_t *sums, int nb) {
+                                                              int64_t *sums, int nb, int32_t *classes) {
     __shared__ int64_t ws[33];
+    __shared__ int own[kOrderClasses];
+    static_assert(kScanThreads == kOrderClasses, "one class per thread");
+    own[threadIdx.x] = 0;
+    __syncthreads();
     const int base = blockIdx.x * kScanBlock + threadIdx.x * kScanItems;
     int64_t sg = 0, sb = 0;
 #pragma unroll
     for (int i = 0; i < kScanItems; ++i)
-        if (base + i < n) { sg += gc[base + i]; sb += bc[base + i]; }
+    {
+        const bool in = base + i < n;
+        const int g = in ? gc[base + i] : 0;
+        sg += g;
+        if (in) sb += bc[base + i];
+        order_count(own, in, g);
+    }
     int64_t tg, tb;
     block_exclusive_scan<int64_t>(sg, tg, ws);
     block_exclusive_scan<int64_t>(sb, tb, ws);
     if (threadIdx.x == 0) { sums[blockIdx.x] = tg; sums[nb + blockIdx.x] = tb; }
+    if (own[threadIdx.x]) atomicAdd(&classes[threadIdx.x], own[threadIdx.x]);  // (the scans above are barriers)
 }
 
-// exclusive scan of the block sums (one block), totals into the counters
-__global__ void __launch_bounds__(1024) k_scan_top(int64_t *sums, int nb, int64_t *counters) {
+// exclusive scan of the block sums (one block), totals into the counters; the
+// tiles per class become the classes' first places in the order
+__global__ void __launch_bounds__(1024) k_scan_top(int64_t *sums, int nb, int64_t *counters, int32_t *classes) {
     __shared__ int64_t ws[33];
+    {
+        const int c = threadIdx.x;
+        int64_t tot;
+        const int64_t ex = block_exclusive_scan<int64_t>(c < kOrderClasses ? classes[c] : 0, tot, ws);
+        if (c < kOrderClasses) classes[c] = (int32_t)ex;
+    }
     for (int which = 0; which < 2; ++which) {
         int64_t carry = 0;
         int64_t *s = sums + (int64_t)which * nb;
@@ -121,13 +167,29 @@ __device__ __forceinline__ void scan_read(const int32_t *cnt, int base, int n, i
 __global__ void __launch_bounds__(kScanThreads) k_scan_down(int32_t *gc, int32_t *gs, int32_t *gcur, int32_t *bc,
                                                             int32_t *bs, int32_t *bcur, const int64_t *sums,
                                                             int n, int nb, int64_t cap_g, int64_t cap_b,
-                                                            int64_t *counters) {
+                                                            int64_t *counters, int32_t *classes, int32_t *order) {
     __shared__ int64_t ws[33];
+    __shared__ int own[kOrderClasses];
+    own[threadIdx.x] = 0;
+    __syncthreads();
     const int base = blockIdx.x * kScanBlock + threadIdx.x * kScanItems;
     for (int which = 0; which < 2; ++which) {
         int32_t *cnt = which == 0 ? gc : bc;
         int32_t v[kScanItems];
         scan_read(cnt, base, n, v);
+        if (which == 0) {  // the tiles' places in the order
+            int rank[kScanItems];
+#pragma unroll
+            for (int i = 0; i < kScanItems; ++i) rank[i] = order_count(own, base + i < n, v[i]);
+            __syncthreads();
+            const int mine = own[threadIdx.x];
+            __syncthreads();
+            if (mine) own[threadIdx.x] = atomicAdd(&classes[threadIdx.x], mine);
+            __syncthreads();
+#pragma unroll
+            for (int i = 0; i < kScanItems; ++i)
+                if (base + i < n) order[own[order_class(v[i])] + rank[i]] = base + i;
+        }
         int64_t s = 0, tot;
 #pragma unroll
         for (int i = 0; i < kScanItems; ++i) s += v[i];
@@ -137,21 +199,57 @@ __global__ void __launch_bounds__(kScanThreads) k_scan_down(int32_t *gc, int32_t
     }
 }
 
-// The whole scan in one launch, a workgroup of 1024 threads per list kind, for
-// up to kScanOne tiles: all counts are loaded at once, four per thread in each
-// of four rounds of 4096 tiles, whose scans then follow each other.  10000
-// tiles: 7 us, where the other path's three launches take 14 and two gaps.
+// The tile order and the whole scan in one launch of three workgroups of 1024
+// threads, for up to kScanOne tiles: the order, the Gaussian lists and the
+// boundary lists.  All counts are loaded at once, four per thread in each of
+// four rounds of 4096 tiles, whose scans then follow each other.  10000
+// tiles: 9 us, where the other path's three launches take 19 and two gaps.
 constexpr int kScanRounds = 4, kScanOne = 1024 * kScanItems * kScanRounds;
+constexpr int kOrderFrom = 1024;  // fewer tiles are on the chip at once, in whatever order
 
 __global__ void __launch_bounds__(1024) k_scan_one(int32_t *gc, int32_t *gs, int32_t *gcur, int32_t *bc, int32_t *bs,
                                                    int32_t *bcur, int n, int64_t cap_g, int64_t cap_b,
-                                                   int64_t *counters) {
+                                                   int64_t *counters, int32_t *order) {
     __shared__ int64_t ws[33];
-    const bool g = blockIdx.x == 0;
+    const bool g = blockIdx.x != 2;  // (0: order, 1: Gaussian lists, 2: boundary lists)
     int32_t *cnt = g ? gc : bc;
     int32_t v[kScanRounds][kScanItems];
 #pragma unroll
     for (int r = 0; r < kScanRounds; ++r) scan_read(cnt, (r * 1024 + threadIdx.x) * kScanItems, n, v[r]);
+    if (blockIdx.x == 0) {
+        // (the counts may be cut at the capacity by the next workgroup
+        // meanwhile: each is read once, so the places are a permutation all the same)
+        __shared__ int own[kOrderClasses];
+        __shared__ uint16_t place[kScanOne];  // the order, put together here and stored in runs
+        if (n <= kOrderFrom) {
+            if ((int)threadIdx.x < n) order[threadIdx.x] = threadIdx.x;
+            return;
+        }
+        int rank[kScanRounds][kScanItems];
+        if (threadIdx.x < kOrderClasses) own[threadIdx.x] = 0;
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < kScanRounds; ++r)
+            if (r * 1024 * kScanItems < n)
+#pragma unroll
+                for (int i = 0; i < kScanItems; ++i)
+                    rank[r][i] = order_count(own, (r * 1024 + (int)threadIdx.x) * kScanItems + i < n, v[r][i]);
+        __syncthreads();
+        int64_t tot;
+        const int64_t ex = block_exclusive_scan<int64_t>(threadIdx.x < kOrderClasses ? own[threadIdx.x] : 0, tot, ws);
+        if (threadIdx.x < kOrderClasses) own[threadIdx.x] = (int)ex;
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < kScanRounds; ++r)
+#pragma unroll
+            for (int i = 0; i < kScanItems; ++i) {
+                const int t = (r * 1024 + (int)threadIdx.x) * kScanItems + i;
+                if (t < n) place[own[order_class(v[r][i])] + rank[r][i]] = (uint16_t)t;
+            }
+        __syncthreads();
+        for (int i = threadIdx.x; i < n; i += 1024) order[i] = place[i];
+        return;
+    }
     int64_t carry = 0;
     bool ovf = false;
 #pragma unroll
@@ -822,17 +920,18 @@ hipError_t launch_binning(const Consts &k, const ViewTable &vt, const StatePtrs 
                           hipStream_t s) {
     const int n = vt.total_tiles;
     if (n <= kScanOne) {
-        hipLaunchKernelGGL(k_scan_one, dim3(2), dim3(1024), 0, s, st.g_count, st.g_start, st.g_cursor, st.b_count,
-                           st.b_start, st.b_cursor, n, k.cap_g, k.cap_b, st.counters);
+        hipLaunchKernelGGL(k_scan_one, dim3(3), dim3(1024), 0, s, st.g_count, st.g_start, st.g_cursor, st.b_count,
+                           st.b_start, st.b_cursor, n, k.cap_g, k.cap_b, st.counters, st.order);
     } else {
+        int32_t *classes = (int32_t *)(st.counters + kOrderWord);
         const int nb = (n + kScanBlock - 1) / kScanBlock;
         int64_t *sums = (int64_t *)st.scan_tmp;
         hipLaunchKernelGGL(k_scan_reduce, dim3(nb), dim3(kScanThreads), 0, s, (const int32_t *)st.g_count,
-                           (const int32_t *)st.b_count, n, sums, nb);
-        hipLaunchKernelGGL(k_scan_top, dim3(1), dim3(1024), 0, s, sums, nb, st.counters);
+                           (const int32_t *)st.b_count, n, sums, nb, classes);
+        hipLaunchKernelGGL(k_scan_top, dim3(1), dim3(1024), 0, s, sums, nb, st.counters, classes);
         hipLaunchKernelGGL(k_scan_down, dim3(nb), dim3(kScanThreads), 0, s, st.g_count, st.g_start, st.g_cursor,
                            st.b_count, st.b_start, st.b_cursor, (const int64_t *)sums, n, nb, k.cap_g, k.cap_b,
-                           st.counters);
+                           st.counters, classes, st.order);
     }
     hipLaunchKernelGGL(k_scatter, dim3((unsigned)((vt.total_b8 + 3) / 4)), dim3(256), 0, s, k, vt, st);
     const int lat_per_view = k.P * k.NL;

@@ -35,7 +35,11 @@ enum Counter {
 // 160,000 waves adding to one address serialize on it.
 constexpr int kStripes = 64;
 constexpr int kStripeStride = 8;  // int64 words per slot
-constexpr int kCounterWords = C_NUM + kStripes * kStripeStride;
+// After them the tiles per length class of their Gaussian list (int32, longest
+// class first), then the classes' cursors into the tile order.
+constexpr int kOrderClasses = 256;
+constexpr int kOrderWord = C_NUM + kStripes * kStripeStride;
+constexpr int kCounterWords = kOrderWord + kOrderClasses / 2;
 
 // per-pixel flags
 constexpr uint8_t PF_VALID = 1;     // the pixel has a Gaussian
@@ -254,6 +258,7 @@ struct StatePtrs {
     double *brec64;        // [pixels][3] boundary points in FP64: mu - pixel centre (x, y), sigma
     int32_t *big_tris;     // [cap_big] queue of raster items
     int32_t *scan_tmp;     // block sums
+    int32_t *order;        // [tiles] the tiles, longest Gaussian lists first (see order_class)
 };
 
 __device__ __forceinline__ int pack16(int lo, int hi) { return (lo & 0xFFFF) | (hi << 16); }
