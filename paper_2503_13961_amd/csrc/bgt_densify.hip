@@ -3,13 +3,12 @@
 // decision, and the rebuilt parameter arrays in which a split patch is
 // replaced by its four midpoint children.
 //
-// Pixel statistics run one thread per pixel; a wave groups its lanes by
-// (patch, view) and adds each group's totals with one atomic per array, so a
-// patch covering a few hundred pixels costs a few atomics per wave rather
-// than one per pixel.  The children's control nets are blossoms of the
-// parent's net at the corners of their sub-domains, taken by de Casteljau
-// steps in FP64.
+// Pixel statistics are summed per patch over 32x32 pixel regions and added
+// with one atomic per (region, patch) and array.  The children's control nets
+// are blossoms of the parent's net at the corners of their sub-domains, taken
+// by de Casteljau steps in FP64.
 #include "bgt_internal.h"
+#include "bgt_wave.h"
 
 namespace bgt {
 
@@ -26,62 +25,117 @@ __device__ __forceinline__ float grey255(const float *img, int64_t pix) {
 
 }  // namespace
 
-// Visibility (views, sub-triangle texels) and the edge prior, per pixel.
+// x of all lanes or'ed together (DPP shifts within 16-lane rows, then across
+// them), in every lane
+__device__ __forceinline__ unsigned wave_or(unsigned x) {
+#define BGT_OR(CTRL, ROWS) x |= (unsigned)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, ROWS, 0xF, true)
+    BGT_OR(0x111, 0xF);  // row_shr:1, 2, 4, 8
+    BGT_OR(0x112, 0xF);
+    BGT_OR(0x114, 0xF);
+    BGT_OR(0x118, 0xF);
+    BGT_OR(0x142, 0xA);  // row_bcast:15, 31
+    BGT_OR(0x143, 0xC);
+#undef BGT_OR
+    return (unsigned)__builtin_amdgcn_readlane((int)x, 63);
+}
+
+// Visibility (views, sub-triangle texels) and the edge prior.  A workgroup
+// takes a 32x32 pixel region of a view, a wave an 8x8 block at a time; a
+// block's totals per patch go to a table in LDS, and the region's to memory at
+// the end.  What bounded it were the atomics: one per (64 pixels of a row,
+// patch) in each of four arrays; a region has a tenth of them: 176 -> 46 us for
+// 16 views of 800x800 with 2000 patches.  The grey levels of the region and
+// its rim are staged in LDS once (one read of the target per pixel).
 __global__ void __launch_bounds__(kThreads) k_stats_pixels(ViewTable vt, int L2, const int32_t *I_tri,
                                                            const float *targets, StatsPtrs sp) {
-    const int64_t pix = blockIdx.x * (int64_t)kThreads + threadIdx.x;
-    const int lane = threadIdx.x & 63;
-    int key = -1, g = 0, s = 0, v = 0;
-    float e = 0.f;
-    if (pix < vt.total_px) {
-        const int tri = I_tri[pix];
-        if (tri >= 0) {
-            v = view_of_pixel(vt, (int)pix);
-            g = tri / L2;
-            s = tri - g * L2;
-            key = g * BGT_MAX_VIEWS + v;
-            if (targets) {
-                // Sobel magnitude of the grey level; 0 on the view's border
-                const ViewInfo &vi = vt.v[v];
-                const int lp = (int)(pix - vi.px_off), x = lp % vi.W, y = lp / vi.W;
-                if (x > 0 && y > 0 && x + 1 < vi.W && y + 1 < vi.H) {
-                    const int64_t c = pix;
-                    const int64_t W = vi.W;
-                    const float a = grey255(targets, c - W - 1), b = grey255(targets, c - W),
-                                cc = grey255(targets, c - W + 1), d = grey255(targets, c - 1),
-                                f = grey255(targets, c + 1), gg = grey255(targets, c + W - 1),
-                                h = grey255(targets, c + W), i = grey255(targets, c + W + 1);
-                    const float gx = (cc + 2.f * f + i) - (a + 2.f * d + gg);
-                    const float gy = (gg + 2.f * h + i) - (a + 2.f * b + cc);
-                    e = sqrtf(gx * gx + gy * gy);
+    constexpr int SLOTS = 64, GW = kRegion + 2;
+    __shared__ int slot_prim[SLOTS];
+    __shared__ unsigned long long tex[SLOTS];
+    __shared__ float edge[SLOTS];
+    __shared__ int count[SLOTS];
+    __shared__ float grey[GW][GW + 1];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    int rx0, ry0;
+    const int v = region_view(vt, blockIdx.x, rx0, ry0);
+    if (v < 0) return;
+    const ViewInfo vi = vt.v[v];
+    constexpr int PASSES = 4;  // 8x8 blocks per wave: block wave + 4 pass of the region's 4x4
+    int tri[PASSES];
+    bool any = false;
+    const int bx = wave * 8 + (lane & 7), by = lane >> 3;
+#pragma unroll
+    for (int i = 0; i < PASSES; ++i) {
+        const int x = rx0 + bx, y = ry0 + by + 8 * i;
+        tri[i] = x < vi.W && y < vi.H ? I_tri[vi.px_off + y * vi.W + x] : -1;
+        any = any || tri[i] >= 0;
+    }
+    if (threadIdx.x < SLOTS) {
+        slot_prim[threadIdx.x] = -1;
+        tex[threadIdx.x] = 0ull;
+        edge[threadIdx.x] = 0.f;
+        count[threadIdx.x] = 0;
+    }
+    if (!__syncthreads_or(any)) return;  // background
+    if (targets) {
+        for (int i = threadIdx.x; i < GW * GW; i += kThreads) {
+            const int gx = i % GW, gy = i / GW, x = rx0 - 1 + gx, y = ry0 - 1 + gy;
+            if (x >= 0 && y >= 0 && x < vi.W && y < vi.H) grey[gy][gx] = grey255(targets, (int64_t)vi.px_off + (int64_t)y * vi.W + x);
+        }
+        __syncthreads();
+    }
+#pragma unroll 1
+    for (int pass = 0; pass < PASSES; ++pass) {
+        const int t = pass == 0 ? tri[0] : (pass == 1 ? tri[1] : (pass == 2 ? tri[2] : tri[3]));
+        const int g = t >= 0 ? t / L2 : -1, s = t >= 0 ? t - g * L2 : 0;
+        const int x = rx0 + bx, y = ry0 + by + 8 * pass;
+        float e = 0.f;
+        if (targets && g >= 0 && x > 0 && y > 0 && x + 1 < vi.W && y + 1 < vi.H) {
+            // Sobel magnitude of the grey level; 0 on the view's border
+            const float *c = &grey[by + 8 * pass + 1][bx + 1];
+            constexpr int W = GW + 1;
+            const float a = c[-W - 1], b = c[-W], cc = c[-W + 1], d = c[-1], f = c[1], gg = c[W - 1], h = c[W], i = c[W + 1];
+            const float gx = (cc + 2.f * f + i) - (a + 2.f * d + gg);
+            const float gy = (gg + 2.f * h + i) - (a + 2.f * b + cc);
+            e = sqrtf(gx * gx + gy * gy);
+        }
+        // per patch of the block
+        for (unsigned long long todo = __ballot(g >= 0); todo;) {
+            const int first = __ffsll((long long)todo) - 1;
+            const int g0 = __builtin_amdgcn_readlane(g, first);
+            const bool mine = g == g0;
+            const unsigned long long m = __ballot(mine);
+            todo &= ~m;
+            const unsigned long long bit = mine ? 1ull << s : 0ull;
+            const unsigned lo = wave_or((unsigned)bit), hi = L2 > 32 ? wave_or((unsigned)(bit >> 32)) : 0u;
+            const unsigned long long bits = (unsigned long long)hi << 32 | lo;
+            float es = mine ? e : 0.f;
+            if (targets) wave_reduce_scatter<1>(&es, lane);  // (the total in lane 0)
+            if (lane == 0) {
+                const int slot = table_slot<SLOTS>(slot_prim, g0);
+                if (slot >= 0) {
+                    atomicOr(&tex[slot], bits);
+                    atomicAdd(&edge[slot], es);
+                    atomicAdd(&count[slot], (int)__popcll(m));
+                } else {  // (the table is full)
+                    atomicOr(&sp.tex[g0], bits);
+                    atomicOr(&sp.view_bits[g0], 1ull << v);
+                    if (targets) {
+                        atomicAdd(&sp.edge_sum[g0], es);
+                        atomicAdd(&sp.edge_cnt[g0], (int)__popcll(m));
+                    }
                 }
             }
         }
     }
-    // one group of lanes per distinct (patch, view)
-    bool pending = key >= 0;
-    while (__any(pending)) {
-        const int first = __ffsll((long long)__ballot(pending)) - 1;
-        const int k0 = __shfl(key, first, 64);
-        const bool mine = pending && key == k0;
-        unsigned long long bits = mine ? (1ull << s) : 0ull;
-        float es = mine ? e : 0.f;
-        int cnt = mine ? 1 : 0;
-#pragma unroll
-        for (int o = 32; o >= 1; o >>= 1) {
-            bits |= __shfl_xor(bits, o, 64);
-            es += __shfl_xor(es, o, 64);
-            cnt += __shfl_xor(cnt, o, 64);
+    __syncthreads();
+    if (threadIdx.x < SLOTS && slot_prim[threadIdx.x] >= 0) {
+        const int g = slot_prim[threadIdx.x];
+        atomicOr(&sp.tex[g], tex[threadIdx.x]);
+        atomicOr(&sp.view_bits[g], 1ull << v);
+        if (targets) {
+            atomicAdd(&sp.edge_sum[g], edge[threadIdx.x]);
+            atomicAdd(&sp.edge_cnt[g], count[threadIdx.x]);
         }
-        if (lane == first) {
-            atomicOr(&sp.tex[g], bits);
-            atomicOr(&sp.view_bits[g], 1ull << v);
-            if (targets) {
-                atomicAdd(&sp.edge_sum[g], es);
-                atomicAdd(&sp.edge_cnt[g], cnt);
-            }
-        }
-        pending = pending && !mine;
     }
 }
 
@@ -267,8 +321,7 @@ __global__ void __launch_bounds__(kThreads) k_apply(int P, int T, int K, PrimPtr
 
 hipError_t launch_stats(const Consts &k, const ViewTable &vt, const int32_t *I_tri, const float *targets,
                         const float *d_ctrl, const StatsPtrs &sp, hipStream_t s) {
-    const int64_t blocks = ((int64_t)vt.total_px + kThreads - 1) / kThreads;
-    hipLaunchKernelGGL(k_stats_pixels, dim3((unsigned)blocks), dim3(kThreads), 0, s, vt, k.L2, I_tri, targets, sp);
+    hipLaunchKernelGGL(k_stats_pixels, dim3((unsigned)region_count(vt)), dim3(kThreads), 0, s, vt, k.L2, I_tri, targets, sp);
     hipLaunchKernelGGL(k_stats_prims, dim3((k.P + kThreads - 1) / kThreads), dim3(kThreads), 0, s, k.P, k.ncp, vt.n,
                        d_ctrl, sp);
     return hipGetLastError();

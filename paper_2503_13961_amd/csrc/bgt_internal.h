@@ -325,6 +325,51 @@ struct DensifyRule {
     double tau_g, tau_b, tau_v, tau_r, tau_a, tau_s;
 };
 
+// ---------------------------------------------------------------- pixel regions
+
+// Workgroups that sum over pixels per patch take regions of kRegion px a side
+constexpr int kRegion = 32;
+
+// view, region origin of workgroup `reg` (regions of kRegion px, row-major per view)
+__device__ __forceinline__ int region_view(const ViewTable &vt, int reg, int &rx0, int &ry0) {
+    int acc = 0;
+    for (int v = 0; v < vt.n; ++v) {
+        const int nx = (vt.v[v].W + kRegion - 1) / kRegion, ny = (vt.v[v].H + kRegion - 1) / kRegion;
+        if (reg < acc + nx * ny) {
+            const int l = reg - acc;
+            rx0 = (l % nx) * kRegion;
+            ry0 = (l / nx) * kRegion;
+            return v;
+        }
+        acc += nx * ny;
+    }
+    rx0 = ry0 = 0;
+    return -1;
+}
+
+inline int64_t region_count(const ViewTable &vt) {
+    int64_t n = 0;
+    for (int v = 0; v < vt.n; ++v)
+        n += (int64_t)((vt.v[v].W + kRegion - 1) / kRegion) * ((vt.v[v].H + kRegion - 1) / kRegion);
+    return n;
+}
+
+// Row of primitive p in the workgroup's table, each lane for its own p: open
+// addressing over the rows' primitive ids, claimed by compare-and-swap; -1
+// when kProbes rows from its hash on hold other primitives.
+constexpr int kProbes = 16;
+
+template <int SLOTS>
+__device__ __forceinline__ int table_slot(int *slot_prim, int p) {
+    const int h = (int)(((unsigned)p * 2654435761u) >> 16);
+    for (int n = 0; n < kProbes; ++n) {
+        const int q = (h + n) & (SLOTS - 1);
+        const int old = atomicCAS(&slot_prim[q], -1, p);
+        if (old == -1 || old == p) return q;
+    }
+    return -1;
+}
+
 // ---------------------------------------------------------------- launchers
 
 hipError_t launch_tessellate(const Consts &k, const PrimPtrs &pr, float *verts, hipStream_t s);

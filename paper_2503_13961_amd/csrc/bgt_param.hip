@@ -82,42 +82,8 @@ struct RowDims {
     }
 };
 
-// Row of primitive p in the workgroup's table, each lane for its own p: open
-// addressing over the rows' primitive ids, claimed by compare-and-swap; -1
-// when kProbes rows from its hash on hold other primitives.
-constexpr int kProbes = 16;
-
-template <int SLOTS>
-__device__ __forceinline__ int table_slot(int *slot_prim, int p) {
-    const int h = (int)(((unsigned)p * 2654435761u) >> 16);
-    for (int n = 0; n < kProbes; ++n) {
-        const int q = (h + n) & (SLOTS - 1);
-        const int old = atomicCAS(&slot_prim[q], -1, p);
-        if (old == -1 || old == p) return q;
-    }
-    return -1;
-}
-
-constexpr int kRegion = 32;      // pixels per side of a workgroup's region
 constexpr int kRegionPasses = 4; // 8x8 blocks per wave: (32/8)^2 blocks over 4 waves
 constexpr int kLatPerGroup = 256 * kRegionPasses;
-
-// view, region origin of workgroup `reg` (regions of kRegion px, row-major per view)
-__device__ __forceinline__ int region_view(const ViewTable &vt, int reg, int &rx0, int &ry0) {
-    int acc = 0;
-    for (int v = 0; v < vt.n; ++v) {
-        const int nx = (vt.v[v].W + kRegion - 1) / kRegion, ny = (vt.v[v].H + kRegion - 1) / kRegion;
-        if (reg < acc + nx * ny) {
-            const int l = reg - acc;
-            rx0 = (l % nx) * kRegion;
-            ry0 = (l / nx) * kRegion;
-            return v;
-        }
-        acc += nx * ny;
-    }
-    rx0 = ry0 = 0;
-    return -1;
-}
 
 // The blend pass's sums g[0..8] of record `rid` of view vi: one per tile its
 // Gaussian was binned to (the tile range of the binning pass), added in
@@ -617,9 +583,7 @@ hipError_t launch_param_bwd(const Consts &k, const ViewTable &vt, const PrimPtrs
                             const StatePtrs &st, const GradPtrs &gr, hipStream_t s) {
     const bool ext = k.T > 1 || k.K > 0;  // resolution-3 maps or SH colour
     // pixel records (in the lattice variant: boundary points only), then the lattice Gaussians
-    int64_t regions = 0;
-    for (int v = 0; v < vt.n; ++v)
-        regions += (int64_t)((vt.v[v].W + kRegion - 1) / kRegion) * ((vt.v[v].H + kRegion - 1) / kRegion);
+    const int64_t regions = region_count(vt);
     for (int lat = 0; lat < (k.NL > 0 ? 2 : 1); ++lat) {
         const int64_t groups = lat ? ((int64_t)vt.n * k.P * k.NL + kLatPerGroup - 1) / kLatPerGroup : regions;
         dim3 grid((unsigned)groups), block(256);
