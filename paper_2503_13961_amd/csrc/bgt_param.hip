@@ -19,8 +19,10 @@
 // rows costs a pass over a block's 64 rows however many primitives it shows
 // (two LDS reads and one FMA per row); a reduce-scatter of the 45 values per
 // primitive cost 180 instructions each, with five primitives a block there.
-// Together 2.24 -> 1.28 ms; 2000 patches in 16 views of 800x800 0.326 ->
-// 0.30 ms, where the waits for the scattered 36-byte sums remain.  In the
+// Together 2.24 -> 1.27 ms; 2000 patches in 16 views of 800x800 0.326 ->
+// 0.28 ms, where the waits for the scattered 36-byte sums remain (of it 0.012 by
+// ending background regions at once and keeping the pass's stores after its
+// loads).  In the
 // lattice variant a second launch walks the lattice Gaussians, 1024
 // consecutive records (about a dozen patches) per workgroup, at their nodes'
 // (u, v).
@@ -166,10 +168,27 @@ __global__ void __launch_bounds__(256, EXT ? 2 : DEG <= 2 ? 4 : 3) k_param_bwd(C
         fb[ch] = rows + b;
     }
     const bool ovf = (st.counters[C_OVERFLOW] & 1) != 0;  // the Gaussian lists overflowed
+    // the wave's pixels: block wave + 4 pass of the region's 4x4 blocks, so that
+    // a lane's column is fixed and its row moves by 8 per pass.  The flags of
+    // all passes are read at once; a region without a Gaussian or boundary
+    // point (two thirds of the regions where an object stands before a
+    // background) ends here.
+    int rv = 0, pix0 = 0, vw = 0;
+    unsigned flags = 0;  // a byte per pass
+    if constexpr (!LAT) {
+        int rx0 = 0, ry0 = 0;
+        rv = region_view(vt, blockIdx.x, rx0, ry0);
+        if (rv < 0) return;
+        vw = vt.v[rv].W;
+        const int vh = vt.v[rv].H, x0 = rx0 + wave * 8 + (lane & 7), y0 = ry0 + (lane >> 3);
+        pix0 = vt.v[rv].px_off + y0 * vw + x0;
+#pragma unroll
+        for (int pass = 0; pass < kRegionPasses; ++pass)
+            if (x0 < vw && y0 + 8 * pass < vh) flags |= (unsigned)st.pflags[pix0 + pass * 8 * vw] << (8 * pass);
+        if (!__syncthreads_or((flags & (PF_VALID * 0x01010101u)) != 0)) return;
+    }
     for (int i = threadIdx.x; i < SLOTS; i += blockDim.x) slot_prim[i] = -1;
     for (int i = threadIdx.x; i < SLOTS * NV; i += blockDim.x) table[i] = 0.f;
-    int rx0 = 0, ry0 = 0, rv = 0;
-    if constexpr (!LAT) rv = region_view(vt, blockIdx.x, rx0, ry0);
     __syncthreads();
 #pragma unroll 1
     for (int pass = 0; pass < kRegionPasses; ++pass) {
@@ -207,17 +226,13 @@ __global__ void __launch_bounds__(256, EXT ? 2 : DEG <= 2 ? 4 : 3) k_param_bwd(C
             pix = vt.total_px + (int)i;
             prim = p;
         }
-    } else if (rv >= 0) {
-        // block wave + 4 pass of the region's 4x4 blocks of 8x8 pixels
-        const int b = wave + 4 * pass;
-        const int x0 = rx0 + (b & 3) * 8 + (lane & 7), y0 = ry0 + (b >> 2) * 8 + (lane >> 3);
+    } else {
         v0 = rv;
-        const int lr = y0 * vt.v[rv].W + x0;
-        if (x0 < vt.v[rv].W && y0 < vt.v[rv].H) pix = vt.v[rv].px_off + lr;
+        if ((flags >> (8 * pass)) & PF_VALID) pix = pix0 + pass * 8 * vw;
     }
+    const bool bnd = !LAT && pix >= 0 && ((flags >> (8 * pass)) & PF_BOUNDARY);
     {
-        const uint8_t fl = (!LAT && pix >= 0) ? st.pflags[pix] : (uint8_t)0;
-        if (pix >= 0 && (LAT || (fl & PF_VALID))) {
+        if (pix >= 0) {
             // the blend sums: moments m0..m4 = sum dG (dx, dy, dx dx, dx dy, dy dy)
             // of dl/dG G, colour, opacity (the record's Gaussian; a pixel
             // record of the lattice variant has none), boundary radius and
@@ -231,12 +246,11 @@ __global__ void __launch_bounds__(256, EXT ? 2 : DEG <= 2 ? 4 : 3) k_param_bwd(C
                 uvp = st.I_uv[pix];
             }
             if constexpr (!LAT) prim = tri / k.L2;
-            if (LAT || k.NL == 0) gauss_sums(k, vt.v[v0], st, pix, ovf, g);
-            if (!LAT && (fl & PF_BOUNDARY)) {  // read and cleared for the next backward pass
-                float *bp = st.dbound + (int64_t)pix * 3;
+            if (bnd) {  // read here and cleared below for the next backward pass
+                const float *bp = st.dbound + (int64_t)pix * 3;
                 g[9] = bp[0]; g[10] = bp[1]; g[11] = bp[2];
-                bp[0] = 0.f; bp[1] = 0.f; bp[2] = 0.f;
             }
+            if (LAT || k.NL == 0) gauss_sums(k, vt.v[v0], st, pix, ovf, g);
             bool nz = false;
 #pragma unroll
             for (int i = 0; i < 12; ++i) nz = nz || g[i] != 0.f;
@@ -446,6 +460,10 @@ __global__ void __launch_bounds__(256, EXT ? 2 : DEG <= 2 ? 4 : 3) k_param_bwd(C
                 }
             }
         }
+    }
+    if (bnd) {  // (after the pass's loads: one issued after a store waits for it too)
+        float *bp = st.dbound + (int64_t)pix * 3;
+        bp[0] = 0.f; bp[1] = 0.f; bp[2] = 0.f;
     }
     // the wave's primitives: first lane, number of lanes, and each lane's row
     // in the order of the primitives
