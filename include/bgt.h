@@ -118,8 +118,9 @@ typedef struct {
 typedef struct {
     int32_t tess_level;    /* L, sub-triangles per patch L^2, 1..8 (default 4) */
     int32_t tile;          /* blending tile side: 8, 16 or 32 (default 16) */
-    int32_t batch;         /* Gaussians staged per LDS batch: 32, 64 or 128, at most tile*tile (at 8 px
-                              32 are staged; 64 takes the variant with room for more boundary points) */
+    int32_t batch;         /* 32, 64 or 128, at most tile*tile: at 8 px 64 takes the variant with LDS for
+                              more boundary points and runs per tile than 32; no effect on larger tiles,
+                              whose waves stage as many Gaussians as suits them */
     int32_t flags;         /* BGT_FLAG_* bits (default 0) */
     float z_near;          /* cull distance along the optical axis (0.2) */
     float g_min;           /* Gaussian support: G >= g_min (2^-15) */

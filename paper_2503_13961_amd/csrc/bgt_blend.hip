@@ -158,6 +158,10 @@ constexpr float kDKink = 1e-6f;
 // that, and the products add a few 1e-7).  Points whose FP32 values are within
 // twice this of the smallest are re-decided from the FP64 records.
 constexpr float kTBand = 9e-6f;
+// A point is in range where d/sigma < 1; where (d/sigma)^2 in FP32 is within
+// 2 kTBand of 1 the ratio itself, the FP32 quotient, decides that.
+constexpr float kTIn = 1.0f - 2.0f * kTBand, kTOut = 1.0f + 2.0f * kTBand;
+constexpr float kRatioBand = 4e-6f;  // bound on |d/sigma in FP32 - in FP64| below 1, as kTBand
 
 // -log2(e)/2: G = exp(-d^T Q d / 2) = 2^(kE d^T Q d)
 constexpr float kE = -0.5f * 1.44269504088896341f;
@@ -228,8 +232,9 @@ struct ArgScan {
         t2 = fminf(t2, fmaxf(t, t1));
         if (t < t1) { t1 = t; e1 = e; }
     }
-    __device__ __forceinline__ bool none() const { return !(t1 < 1.0f); }
-    __device__ __forceinline__ bool ambiguous() const { return t2 < 1.0f && t2 - t1 <= 2.0f * kTBand; }
+    __device__ __forceinline__ bool none() const { return !(t1 < kTOut); }
+    __device__ __forceinline__ bool ambiguous() const { return t2 - t1 <= 2.0f * kTBand; }
+    __device__ __forceinline__ bool edge() const { return t1 + 2.0f * kTBand >= kTIn; }  // (a near-tie can lie out of range)
 };
 
 // d/sigma in FP64 from pixel (x, y) to the boundary point of record bpix,
@@ -273,6 +278,30 @@ __device__ __forceinline__ int arg_min(const BL &B, const StatePtrs &st, int bs0
         }
     }
     if (a.none()) return -1;
+    if (a.edge()) {
+        // (rare) the points in range by their FP32 ratios, near-ties of those in FP64
+        float q1 = 2.0f, q2 = 2.0f;
+        int first = -1, arg = -1;
+        for (int pass = 0; pass < 2; ++pass) {
+            double rb = 2.0;
+            for (int e = e0; e < e1; ++e) {
+                const int bpix = (int)st.b_list[bs0 + e];
+                const float4 p = boundary_point(st, bpix, ox, oy, pm, sg);
+                const float q = __fdiv_rn(sqrtf(point_d2(p, lx, ly)), sg);
+                if (!(q < 1.0f)) continue;
+                if (pass == 0) {
+                    if (q < q1) { q2 = q1; q1 = q; first = e; }
+                    else if (q < q2) q2 = q;
+                } else if (q <= q1 + 2.0f * kRatioBand) {
+                    const int b = __float_as_int(p.w);
+                    const double x = ratio64(st, bpix, lx, ly, lo16(b), hi16(b));
+                    if (x < rb) { rb = x; arg = e; }
+                }
+            }
+            if (pass == 0 && (first < 0 || q2 - q1 > 2.0f * kRatioBand)) return first;
+        }
+        return arg;
+    }
     if (!a.ambiguous()) return a.e1;
     double rb = 2.0;
     int arg = -1;
@@ -280,7 +309,7 @@ __device__ __forceinline__ int arg_min(const BL &B, const StatePtrs &st, int bs0
         const int bpix = (int)st.b_list[bs0 + e];
         const float4 p = boundary_point(st, bpix, ox, oy, pm, sg);
         const float t = point_t(p, lx, ly);
-        if (!(t < 1.0f && t <= a.t1 + 2.0f * kTBand)) continue;
+        if (!(t <= a.t1 + 2.0f * kTBand)) continue;
         const int b = __float_as_int(p.w);
         const double q = ratio64(st, bpix, lx, ly, lo16(b), hi16(b));
         if (q < rb) { rb = q; arg = e; }
@@ -462,7 +491,7 @@ __device__ __forceinline__ RowInfo build_rows(BL &B, const StatePtrs &st, const 
                 }
             }
             float g = 1.0f;
-            if (t < 1.0f) g = gamma_fn(sqrtf(point_d2(B.pt[em], lx, ly)), B.sigma[em]);
+            if (t < kTOut) g = gamma_fn(sqrtf(point_d2(B.pt[em], lx, ly)), B.sigma[em]);  // (at most 1)
             if (bc <= CAP) {
                 g = weight(g, __builtin_amdgcn_readfirstlane(B.run_prim[r]) == h);
             } else {  // (from several chunks: gamma* until the last one)
@@ -610,7 +639,8 @@ __global__ void __launch_bounds__(TS *TS) k_blend_fwd(Consts k, ViewTable vt, St
     constexpr int RM = BL::RM, NW = D::NW, KI = D::KI_FWD;
     __shared__ BL B;
     __shared__ BatchLds<KI> SB[NW];
-    const int t = st.order[blockIdx.x], tid = threadIdx.x, lane = tid & 63, wave = NW > 1 ? __builtin_amdgcn_readfirstlane(tid >> 6) : 0;
+    const int t = st.order[blockIdx.x], tid = threadIdx.x, lane = tid & 63;
+    const int wave = NW > 1 ? __builtin_amdgcn_readfirstlane(tid >> 6) : 0;
     BatchLds<KI> &S = SB[wave];
     const int v = view_of_tile(vt, t);
     const ViewInfo vi = vt.v[v];
@@ -1095,7 +1125,7 @@ k_blend_bwd(Consts k, ViewTable vt, StatePtrs st, RowPool pool, const float *ima
     int cur_gp = lane < wave_last ? P.gp : -1;
     bool wide = false;                    // this lane's entry adds to sums of its own
     unsigned long long staged = 0;        // the staged batch's entries that reach the block
-    auto stage = [&](const SlotPrefetch &Q) {  // Q's record as this lane's entry of the batch; whether it reaches the block
+    auto stage = [&](const SlotPrefetch &Q) {  // Q's record as this lane's entry; whether it reaches the block
         wide = !narrow_range(__float_as_int(Q.r3.x), __float_as_int(Q.r3.y), TSH);
         const int bits = stage_slot(S, Q, lane, wx0, wy0, B, R, kappa, wave);
         if constexpr (ONE) S.c[lane].w = __int_as_float(wide ? ~Q.gp : Q.gp);
@@ -1164,7 +1194,8 @@ k_blend_bwd(Consts k, ViewTable vt, StatePtrs st, RowPool pool, const float *ima
             // slowest never waits for another
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
             int before = 0;
-            if (lane == 0) before = __hip_atomic_fetch_add(&ring_done[slot], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            if (lane == 0)
+                before = __hip_atomic_fetch_add(&ring_done[slot], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
             if (__builtin_amdgcn_readfirstlane(before) == NW * (gen + 1) - 1) {
                 __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
                 int gp = prev_gp;
@@ -1190,7 +1221,8 @@ k_blend_bwd(Consts k, ViewTable vt, StatePtrs st, RowPool pool, const float *ima
                     for (int f = 0; f < kSums; ++f) a[f] = 0.f;
                 }
                 __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-                if (lane == 0) __hip_atomic_store(&ring_free[slot], gen + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                if (lane == 0)
+                    __hip_atomic_store(&ring_free[slot], gen + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
             }
         }
     }
@@ -1262,13 +1294,14 @@ static hipError_t launch_bwd_t(const Consts &k, const ViewTable &vt, const State
     return hipGetLastError();
 }
 
-// (tile, batch) pairs with a kernel; a batch is loaded by one thread per
-// slot, so it cannot exceed the tile's pixel count
-#define BGT_BLEND_CONFIGS(X) X(8, 32) X(8, 64) X(16, 32) X(16, 64) X(16, 128) X(32, 32) X(32, 64) X(32, 128)
+// (tile, batch) pairs and the kernel they take: `batch` tells the two 8 px
+// variants apart, larger tiles have one kernel
+#define BGT_BLEND_CONFIGS(X) \
+    X(8, 32, 32) X(8, 64, 64) X(16, 32, 64) X(16, 64, 64) X(16, 128, 64) X(32, 32, 64) X(32, 64, 64) X(32, 128, 64)
 
 hipError_t launch_blend_fwd(const Consts &k, const ViewTable &vt, const StatePtrs &st, float *image, hipStream_t s) {
-#define BGT_CASE(TS, K) \
-    if (k.tile == TS && k.batch == K) return launch_fwd_t<TS, K>(k, vt, st, image, s);
+#define BGT_CASE(TS, BATCH, K) \
+    if (k.tile == TS && k.batch == BATCH) return launch_fwd_t<TS, K>(k, vt, st, image, s);
     BGT_BLEND_CONFIGS(BGT_CASE)
 #undef BGT_CASE
     return hipErrorInvalidValue;
@@ -1276,8 +1309,8 @@ hipError_t launch_blend_fwd(const Consts &k, const ViewTable &vt, const StatePtr
 
 hipError_t launch_blend_bwd(const Consts &k, const ViewTable &vt, const StatePtrs &st, const float *image,
                             const float *grad_image, hipStream_t s) {
-#define BGT_CASE(TS, K) \
-    if (k.tile == TS && k.batch == K) return launch_bwd_t<TS, K>(k, vt, st, image, grad_image, s);
+#define BGT_CASE(TS, BATCH, K) \
+    if (k.tile == TS && k.batch == BATCH) return launch_bwd_t<TS, K>(k, vt, st, image, grad_image, s);
     BGT_BLEND_CONFIGS(BGT_CASE)
 #undef BGT_CASE
     return hipErrorInvalidValue;
