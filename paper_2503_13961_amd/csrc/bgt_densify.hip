@@ -40,15 +40,21 @@ __device__ __forceinline__ unsigned wave_or(unsigned x) {
 }
 
 // Visibility (views, sub-triangle texels) and the edge prior.  A workgroup
-// takes a 32x32 pixel region of a view, a wave an 8x8 block at a time; a
-// block's totals per patch go to a table in LDS, and the region's to memory at
-// the end.  What bounded it were the atomics: one per (64 pixels of a row,
-// patch) in each of four arrays; a region has a tenth of them: 176 -> 46 us for
-// 16 views of 800x800 with 2000 patches.  The grey levels of the region and
-// its rim are staged in LDS once (one read of the target per pixel).
+// takes a region of a view, 16 PASSES / 2 px a side, a wave an 8x8 block at a
+// time; a block's totals per patch go to a table in LDS, and the region's to
+// memory at the end.  What bounded it were the atomics: one per (64 pixels of a
+// row, patch) in each of four arrays; a 32x32 region has a tenth of them:
+// 176 -> 46 us for 16 views of 800x800 with 2000 patches.  The grey levels of
+// the region and its rim are staged in LDS once (one read of the target per
+// pixel).  A block of up to three patches sums each over the wave; with more
+// every lane adds its own pixel to the table, which takes the same time
+// however many there are.
+template <int PASSES>
 __global__ void __launch_bounds__(kThreads) k_stats_pixels(ViewTable vt, int L2, const int32_t *I_tri,
                                                            const float *targets, StatsPtrs sp) {
-    constexpr int SLOTS = 64, GW = kRegion + 2;
+    static_assert(PASSES == 4 || PASSES == 1, "regions of 32 or 16 px");
+    constexpr int SIDE = PASSES == 4 ? 32 : 16, BW = SIDE / 8;  // 8x8 blocks per row of the region
+    constexpr int SLOTS = kThreads, GW = SIDE + 2;
     __shared__ int slot_prim[SLOTS];
     __shared__ unsigned long long tex[SLOTS];
     __shared__ float edge[SLOTS];
@@ -56,36 +62,50 @@ __global__ void __launch_bounds__(kThreads) k_stats_pixels(ViewTable vt, int L2,
     __shared__ float grey[GW][GW + 1];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     int rx0, ry0;
-    const int v = region_view(vt, blockIdx.x, rx0, ry0);
+    const int v = region_view(vt, blockIdx.x, SIDE, rx0, ry0);
     if (v < 0) return;
     const ViewInfo vi = vt.v[v];
-    constexpr int PASSES = 4;  // 8x8 blocks per wave: block wave + 4 pass of the region's 4x4
     int tri[PASSES];
     bool any = false;
-    const int bx = wave * 8 + (lane & 7), by = lane >> 3;
+    // block wave + 4 pass of the region
+    const int bx = (wave % BW) * 8 + (lane & 7), by = (wave / BW) * 8 + (lane >> 3);
 #pragma unroll
     for (int i = 0; i < PASSES; ++i) {
         const int x = rx0 + bx, y = ry0 + by + 8 * i;
         tri[i] = x < vi.W && y < vi.H ? I_tri[vi.px_off + y * vi.W + x] : -1;
         any = any || tri[i] >= 0;
     }
-    if (threadIdx.x < SLOTS) {
-        slot_prim[threadIdx.x] = -1;
-        tex[threadIdx.x] = 0ull;
-        edge[threadIdx.x] = 0.f;
-        count[threadIdx.x] = 0;
-    }
+    slot_prim[threadIdx.x] = -1;
+    tex[threadIdx.x] = 0ull;
+    edge[threadIdx.x] = 0.f;
+    count[threadIdx.x] = 0;
     if (!__syncthreads_or(any)) return;  // background
     if (targets) {
         for (int i = threadIdx.x; i < GW * GW; i += kThreads) {
             const int gx = i % GW, gy = i / GW, x = rx0 - 1 + gx, y = ry0 - 1 + gy;
-            if (x >= 0 && y >= 0 && x < vi.W && y < vi.H) grey[gy][gx] = grey255(targets, (int64_t)vi.px_off + (int64_t)y * vi.W + x);
+            if (x >= 0 && y >= 0 && x < vi.W && y < vi.H)
+                grey[gy][gx] = grey255(targets, (int64_t)vi.px_off + (int64_t)y * vi.W + x);
         }
         __syncthreads();
     }
-#pragma unroll 1
+    auto add = [&](int g, unsigned long long bits, float es, int n) {
+        const int slot = table_slot<SLOTS>(slot_prim, g);
+        if (slot >= 0) {
+            atomicOr(&tex[slot], bits);
+            atomicAdd(&edge[slot], es);
+            atomicAdd(&count[slot], n);
+        } else {  // (the table is full)
+            atomicOr(&sp.tex[g], bits);
+            atomicOr(&sp.view_bits[g], 1ull << v);
+            if (targets) {
+                atomicAdd(&sp.edge_sum[g], es);
+                atomicAdd(&sp.edge_cnt[g], n);
+            }
+        }
+    };
+#pragma unroll
     for (int pass = 0; pass < PASSES; ++pass) {
-        const int t = pass == 0 ? tri[0] : (pass == 1 ? tri[1] : (pass == 2 ? tri[2] : tri[3]));
+        const int t = tri[pass];
         const int g = t >= 0 ? t / L2 : -1, s = t >= 0 ? t - g * L2 : 0;
         const int x = rx0 + bx, y = ry0 + by + 8 * pass;
         float e = 0.f;
@@ -93,42 +113,35 @@ __global__ void __launch_bounds__(kThreads) k_stats_pixels(ViewTable vt, int L2,
             // Sobel magnitude of the grey level; 0 on the view's border
             const float *c = &grey[by + 8 * pass + 1][bx + 1];
             constexpr int W = GW + 1;
-            const float a = c[-W - 1], b = c[-W], cc = c[-W + 1], d = c[-1], f = c[1], gg = c[W - 1], h = c[W], i = c[W + 1];
+            const float a = c[-W - 1], b = c[-W], cc = c[-W + 1], d = c[-1], f = c[1];
+            const float gg = c[W - 1], h = c[W], i = c[W + 1];
             const float gx = (cc + 2.f * f + i) - (a + 2.f * d + gg);
             const float gy = (gg + 2.f * h + i) - (a + 2.f * b + cc);
             e = sqrtf(gx * gx + gy * gy);
         }
-        // per patch of the block
-        for (unsigned long long todo = __ballot(g >= 0); todo;) {
-            const int first = __ffsll((long long)todo) - 1;
-            const int g0 = __builtin_amdgcn_readlane(g, first);
+        const unsigned long long all = __ballot(g >= 0), own = 1ull << s;
+        unsigned long long more = all;  // lanes beyond the first three patches
+#pragma unroll
+        for (int n = 0; n < 3; ++n)
+            if (more) more &= ~__ballot(g == __builtin_amdgcn_readlane(g, __ffsll((long long)more) - 1));
+        if (more) {
+            if (g >= 0) add(g, own, e, 1);
+            continue;
+        }
+        for (unsigned long long todo = all; todo;) {
+            const int g0 = __builtin_amdgcn_readlane(g, __ffsll((long long)todo) - 1);
             const bool mine = g == g0;
             const unsigned long long m = __ballot(mine);
             todo &= ~m;
-            const unsigned long long bit = mine ? 1ull << s : 0ull;
+            const unsigned long long bit = mine ? own : 0ull;
             const unsigned lo = wave_or((unsigned)bit), hi = L2 > 32 ? wave_or((unsigned)(bit >> 32)) : 0u;
-            const unsigned long long bits = (unsigned long long)hi << 32 | lo;
             float es = mine ? e : 0.f;
             if (targets) wave_reduce_scatter<1>(&es, lane);  // (the total in lane 0)
-            if (lane == 0) {
-                const int slot = table_slot<SLOTS>(slot_prim, g0);
-                if (slot >= 0) {
-                    atomicOr(&tex[slot], bits);
-                    atomicAdd(&edge[slot], es);
-                    atomicAdd(&count[slot], (int)__popcll(m));
-                } else {  // (the table is full)
-                    atomicOr(&sp.tex[g0], bits);
-                    atomicOr(&sp.view_bits[g0], 1ull << v);
-                    if (targets) {
-                        atomicAdd(&sp.edge_sum[g0], es);
-                        atomicAdd(&sp.edge_cnt[g0], (int)__popcll(m));
-                    }
-                }
-            }
+            if (lane == 0) add(g0, (unsigned long long)hi << 32 | lo, es, (int)__popcll(m));
         }
     }
     __syncthreads();
-    if (threadIdx.x < SLOTS && slot_prim[threadIdx.x] >= 0) {
+    if (slot_prim[threadIdx.x] >= 0) {
         const int g = slot_prim[threadIdx.x];
         atomicOr(&sp.tex[g], tex[threadIdx.x]);
         atomicOr(&sp.view_bits[g], 1ull << v);
@@ -321,7 +334,14 @@ __global__ void __launch_bounds__(kThreads) k_apply(int P, int T, int K, PrimPtr
 
 hipError_t launch_stats(const Consts &k, const ViewTable &vt, const int32_t *I_tri, const float *targets,
                         const float *d_ctrl, const StatsPtrs &sp, hipStream_t s) {
-    hipLaunchKernelGGL(k_stats_pixels, dim3((unsigned)region_count(vt)), dim3(kThreads), 0, s, vt, k.L2, I_tri, targets, sp);
+    // regions of 32 px where they make the chip four workgroups per CU, else of 16:
+    // a single small view is bound by one workgroup's time, not by atomics
+    if (region_count(vt, 32) >= 1024)
+        hipLaunchKernelGGL(k_stats_pixels<4>, dim3((unsigned)region_count(vt, 32)), dim3(kThreads), 0, s, vt, k.L2, I_tri,
+                           targets, sp);
+    else
+        hipLaunchKernelGGL(k_stats_pixels<1>, dim3((unsigned)region_count(vt, 16)), dim3(kThreads), 0, s, vt, k.L2, I_tri,
+                           targets, sp);
     hipLaunchKernelGGL(k_stats_prims, dim3((k.P + kThreads - 1) / kThreads), dim3(kThreads), 0, s, k.P, k.ncp, vt.n,
                        d_ctrl, sp);
     return hipGetLastError();

@@ -682,8 +682,8 @@ constexpr int kScalarPatches = 2;  // see k_gen
 
 // (waves per SIMD: as many as the registers allow without spilling)
 template <int DEG, bool EXT>
-__global__ void __launch_bounds__(256, DEG == 5 ? 3 : EXT || DEG == 4 ? 4 : 5) k_gen(Consts k, ViewTable vt, PrimPtrs pr, const float *cams, StatePtrs st,
-                                             const float *__restrict__ patch) {
+__global__ void __launch_bounds__(256, DEG == 5 ? 3 : EXT || DEG == 4 ? 4 : 5)
+k_gen(Consts k, ViewTable vt, PrimPtrs pr, const float *cams, StatePtrs st, const float *__restrict__ patch) {
     constexpr int NCP = (DEG + 1) * (DEG + 2) / 2;
     constexpr int MO = patch_m_off(NCP);
     const int PD = k.pdw;

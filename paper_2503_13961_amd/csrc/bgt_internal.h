@@ -327,18 +327,16 @@ struct DensifyRule {
 
 // ---------------------------------------------------------------- pixel regions
 
-// Workgroups that sum over pixels per patch take regions of kRegion px a side
-constexpr int kRegion = 32;
-
-// view, region origin of workgroup `reg` (regions of kRegion px, row-major per view)
-__device__ __forceinline__ int region_view(const ViewTable &vt, int reg, int &rx0, int &ry0) {
+// view (-1: none), region origin of workgroup `reg`: regions of `side` px,
+// row-major per view
+__device__ __forceinline__ int region_view(const ViewTable &vt, int reg, int side, int &rx0, int &ry0) {
     int acc = 0;
     for (int v = 0; v < vt.n; ++v) {
-        const int nx = (vt.v[v].W + kRegion - 1) / kRegion, ny = (vt.v[v].H + kRegion - 1) / kRegion;
+        const int nx = (vt.v[v].W + side - 1) / side, ny = (vt.v[v].H + side - 1) / side;
         if (reg < acc + nx * ny) {
             const int l = reg - acc;
-            rx0 = (l % nx) * kRegion;
-            ry0 = (l / nx) * kRegion;
+            rx0 = (l % nx) * side;
+            ry0 = (l / nx) * side;
             return v;
         }
         acc += nx * ny;
@@ -346,11 +344,9 @@ __device__ __forceinline__ int region_view(const ViewTable &vt, int reg, int &rx
     rx0 = ry0 = 0;
     return -1;
 }
-
-inline int64_t region_count(const ViewTable &vt) {
+inline int64_t region_count(const ViewTable &vt, int side) {
     int64_t n = 0;
-    for (int v = 0; v < vt.n; ++v)
-        n += (int64_t)((vt.v[v].W + kRegion - 1) / kRegion) * ((vt.v[v].H + kRegion - 1) / kRegion);
+    for (int v = 0; v < vt.n; ++v) n += (int64_t)((vt.v[v].W + side - 1) / side) * ((vt.v[v].H + side - 1) / side);
     return n;
 }
 

@@ -84,6 +84,7 @@ struct RowDims {
     }
 };
 
+constexpr int kRegion = 32;      // pixels per side of a workgroup's region
 constexpr int kRegionPasses = 4; // 8x8 blocks per wave: (32/8)^2 blocks over 4 waves
 constexpr int kLatPerGroup = 256 * kRegionPasses;
 
@@ -146,8 +147,8 @@ __device__ __forceinline__ void gauss_sums(const Consts &k, const ViewInfo &vi, 
 
 // (waves per SIMD: as many as the registers allow without spilling)
 template <int DEG, bool EXT, bool LAT>
-__global__ void __launch_bounds__(256, EXT ? 2 : DEG <= 2 ? 4 : 3) k_param_bwd(Consts k, ViewTable vt, PrimPtrs pr, const float *cams,
-                                                                    StatePtrs st, const float *__restrict__ patch) {
+__global__ void __launch_bounds__(256, EXT ? 2 : DEG <= 2 ? 4 : 3)
+k_param_bwd(Consts k, ViewTable vt, PrimPtrs pr, const float *cams, StatePtrs st, const float *__restrict__ patch) {
     constexpr int NCP = (DEG + 1) * (DEG + 2) / 2;
     constexpr int QO = patch_q_off(NCP);
     const int PD = k.pdw;
@@ -177,7 +178,7 @@ __global__ void __launch_bounds__(256, EXT ? 2 : DEG <= 2 ? 4 : 3) k_param_bwd(C
     unsigned flags = 0;  // a byte per pass
     if constexpr (!LAT) {
         int rx0 = 0, ry0 = 0;
-        rv = region_view(vt, blockIdx.x, rx0, ry0);
+        rv = region_view(vt, blockIdx.x, kRegion, rx0, ry0);
         if (rv < 0) return;
         vw = vt.v[rv].W;
         const int vh = vt.v[rv].H, x0 = rx0 + wave * 8 + (lane & 7), y0 = ry0 + (lane >> 3);
@@ -476,7 +477,8 @@ __global__ void __launch_bounds__(256, EXT ? 2 : DEG <= 2 ? 4 : 3) k_param_bwd(C
         const unsigned long long m = __ballot(mine);
         todo &= ~m;
         leaders |= 1ull << l;
-        const int before = (int)__builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, (unsigned)n_rows));
+        const unsigned low = __builtin_amdgcn_mbcnt_lo((unsigned)m, (unsigned)n_rows);
+        const int before = (int)__builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), low);
         if (mine) {
             row = before;
             cnt = __popcll(m);
@@ -601,7 +603,7 @@ hipError_t launch_param_bwd(const Consts &k, const ViewTable &vt, const PrimPtrs
                             const StatePtrs &st, const GradPtrs &gr, hipStream_t s) {
     const bool ext = k.T > 1 || k.K > 0;  // resolution-3 maps or SH colour
     // pixel records (in the lattice variant: boundary points only), then the lattice Gaussians
-    const int64_t regions = region_count(vt);
+    const int64_t regions = region_count(vt, kRegion);
     for (int lat = 0; lat < (k.NL > 0 ? 2 : 1); ++lat) {
         const int64_t groups = lat ? ((int64_t)vt.n * k.P * k.NL + kLatPerGroup - 1) / kLatPerGroup : regions;
         dim3 grid((unsigned)groups), block(256);
