@@ -44,6 +44,15 @@ static_assert(kTW / kHOut * kIH <= kThreads && kTW * (kTH / kVOut) == kThreads, 
 // Staging: wave w takes the region's rows w, w + 4, ...; lane l columns l and,
 // for the last ten, 64 + l.
 constexpr int kRowsPerWave = (kIH + kThreads / 64 - 1) / (kThreads / 64);
+// A workgroup has CH groups of kThreads threads, each with LDS of its own: one
+// group takes the three channels after each other, or three groups one channel
+// each.  A call of few tiles lasts as long as the chain of barriers in one
+// workgroup, which three groups cut to a third; with many tiles the CUs fill
+// better with small workgroups (one of three groups holds 110 KB of LDS).  Loss and
+// gradient, one group -> three: 21 tiles (167x127) 47.9 -> 30.3 us, 240 (640x480)
+// 53.4 -> 36.5, 520 (800^2) 75.7 -> 74.0, 1040 121 -> 117, 1560 153 -> 161,
+// 3120 271 -> 289.
+constexpr int kGroupTiles = 1024;
 
 }  // namespace
 
@@ -150,12 +159,16 @@ struct StageRows {
 // Window moments, SSIM and its derivative maps; per-workgroup sums of the
 // SSIM map and of the squared error.  16 x 800^2: 0.67-0.75 -> 0.42 ms (615 MB:
 // 0.12 ms at the rate of a large copy; FP64 issue alone 0.21).
-__global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) k_ssim_fwd(LossTable lt, const float *x, const float *y, float *map_a,
-                                                       float *map_b, float *map_c, double *partial) {
-    __shared__ float sx[kIH][kSW], sy[kIH][kSW];
-    __shared__ double hs[kIH][kHW];
-    __shared__ double red[kThreads / 64];
-    const int t = blockIdx.x, tid = threadIdx.x;
+template <int CH>
+__global__ void __launch_bounds__(CH *kThreads) __attribute__((amdgpu_waves_per_eu(CH == 1 ? 4 : 3)))
+k_ssim_fwd(LossTable lt, const float *x, const float *y, float *map_a, float *map_b, float *map_c, double *partial) {
+    __shared__ float sxs[CH][kIH][kSW], sys[CH][kIH][kSW];
+    __shared__ double hss[CH][kIH][kHW];
+    __shared__ double red[CH * kThreads / 64];
+    const int group = CH == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x / kThreads);
+    auto &sx = sxs[group], &sy = sys[group];
+    auto &hs = hss[group];
+    const int t = blockIdx.x, tid = threadIdx.x % kThreads;
     const int v = loss_view_of_tile(lt, t);
     const int W = lt.W[v], H = lt.H[v];
     const int tl = t - lt.tile_off[v], tx = tl % lt.tiles_x[v], ty = tl / lt.tiles_x[v];
@@ -165,14 +178,14 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4
     const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     double s_ssim = 0.0, s_sq = 0.0;
 #pragma unroll 1
-    for (int c = 0; c < 3; ++c) {
-        StageRows sr;
-        sr.load(x + base * 3 + c, 3, gx0, gy0, W, H, lane, wave);
+    for (int c = group; c < 3; c += CH) {
+        StageRows rx, ry;
+        rx.load(x + base * 3 + c, 3, gx0, gy0, W, H, lane, wave);
+        ry.load(y + base * 3 + c, 3, gx0, gy0, W, H, lane, wave);
         // (the last reads of the previous channel's stage were its row sums',
         // before the barrier that its column sums waited at)
-        sr.store(sx, lane, wave);
-        sr.load(y + base * 3 + c, 3, gx0, gy0, W, H, lane, wave);
-        sr.store(sy, lane, wave);
+        rx.store(sx, lane, wave);
+        ry.store(sy, lane, wave);
         __syncthreads();
         const int gx = tx * kTW + c0;
 #pragma unroll
@@ -220,7 +233,7 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4
     }
     const double a = block_sum(s_ssim, red);
     const double b = block_sum(s_sq, red);
-    if (tid == 0) {
+    if (threadIdx.x == 0) {
         partial[2 * (int64_t)t] = a;
         partial[2 * (int64_t)t + 1] = b;
     }
@@ -229,12 +242,16 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4
 // dL/dC = (1 - lambda) 2 (x - y) / n - lambda / n * (W*a + 2 x W*b + y W*c)
 // One map at a time; the next one's values are loaded during the sums.
 // 16 x 800^2: 0.49-0.55 -> 0.33 ms (738 MB: 0.15 ms at the rate of a large copy).
-__global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) k_ssim_grad(LossTable lt, const float *x, const float *y,
-                                                        const float *map_a, const float *map_b,
-                                                        const float *map_c, float *grad) {
-    __shared__ float sm[kIH][kSW];
-    __shared__ double hs[kIH][kHW];
-    const int t = blockIdx.x, tid = threadIdx.x;
+template <int CH>
+__global__ void __launch_bounds__(CH *kThreads) __attribute__((amdgpu_waves_per_eu(CH == 1 ? 4 : 3)))
+k_ssim_grad(LossTable lt, const float *x, const float *y, const float *map_a, const float *map_b, const float *map_c,
+            float *grad) {
+    __shared__ float sms[CH][kIH][kSW];
+    __shared__ double hss[CH][kIH][kHW];
+    const int group = CH == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x / kThreads);
+    auto &sm = sms[group];
+    auto &hs = hss[group];
+    const int t = blockIdx.x, tid = threadIdx.x % kThreads;
     const int v = loss_view_of_tile(lt, t);
     const int W = lt.W[v], H = lt.H[v];
     const int tl = t - lt.tile_off[v], tx = tl % lt.tiles_x[v], ty = tl / lt.tiles_x[v];
@@ -243,11 +260,12 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4
     const int c0 = column_at(tid % kTW), r0 = tid / kTW * kVOut;
     const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     StageRows next;
-    next.load(map_a + base, 1, gx0, gy0, W, H, lane, wave);
+    next.load(map_a + group * plane + base, 1, gx0, gy0, W, H, lane, wave);
     const int gx = tx * kTW + c0, gy0o = ty * kTH + r0;
-    float res[3][kVOut];  // (written together at the end: 12 bytes per pixel)
+    float res[3 / CH][kVOut];  // (written together at the end: 12 bytes per pixel)
 #pragma unroll
-    for (int c = 0; c < 3; ++c) {
+    for (int i = 0; i < 3 / CH; ++i) {
+        const int c = group + i;
         float xv[kVOut], yv[kVOut];
         {
             const float *const xp = hidden(x + base * 3 + c), *const yp = hidden(y + base * 3 + c);
@@ -265,8 +283,8 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4
             next.store(sm, lane, wave);
             __syncthreads();
             const float *map = k == 0 ? map_b : (k == 1 ? map_c : map_a);
-            if (k < 2 || c < 2) next.load(map + (c + (k == 2)) * plane + base, 1, gx0, gy0, W, H, lane, wave);
-            window_rows(lt, hs, tid, [&](int r, int i) { return (double)sm[r][i]; });
+            if (k < 2 || i + 1 < 3 / CH) next.load(map + (c + (k == 2)) * plane + base, 1, gx0, gy0, W, H, lane, wave);
+            window_rows(lt, hs, tid, [&](int r, int j) { return (double)sm[r][j]; });
             __syncthreads();
             window_columns(lt, hs, tid, w[k]);
             // (the stage is free from the barrier above on; hs is written
@@ -275,7 +293,7 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4
 #pragma unroll
         for (int o = 0; o < kVOut; ++o) {
             const double a = xv[o], b = yv[o];
-            res[c][o] = (float)((1.0 - lt.lam) * 2.0 * (a - b) * lt.inv_n -
+            res[i][o] = (float)((1.0 - lt.lam) * 2.0 * (a - b) * lt.inv_n -
                                 lt.lam * lt.inv_n * (w[0][o] + 2.0 * a * w[1][o] + b * w[2][o]));
         }
     }
@@ -283,9 +301,9 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4
 #pragma unroll
     for (int o = 0; o < kVOut; ++o) {
         if (gx >= W || gy0o + o >= H) continue;
-        float *q = gp + (int64_t)((gy0o + o) * W + gx) * 3;
+        float *q = gp + (int64_t)((gy0o + o) * W + gx) * 3 + group;
 #pragma unroll
-        for (int c = 0; c < 3; ++c) q[c] = res[c][o];
+        for (int i = 0; i < 3 / CH; ++i) q[i] = res[i][o];
     }
 }
 
@@ -316,16 +334,25 @@ __global__ void __launch_bounds__(kFinal) k_loss_final(const double *partial, in
     }
 }
 
-hipError_t launch_loss(const LossTable &lt, const float *x, const float *y, float *loss, float *grad, float *maps,
-                       double *partial, hipStream_t s) {
+template <int CH>
+static void loss_passes(const LossTable &lt, const float *x, const float *y, float *loss, float *grad, float *maps,
+                        double *partial, hipStream_t s) {
     const int64_t n = 3 * (int64_t)lt.total_px;
     float *ma = maps, *mb = maps + n, *mc = maps + 2 * n;
-    hipLaunchKernelGGL(k_ssim_fwd, dim3(lt.total_tiles), dim3(kThreads), 0, s, lt, x, y, ma, mb, mc, partial);
+    hipLaunchKernelGGL(k_ssim_fwd<CH>, dim3(lt.total_tiles), dim3(CH * kThreads), 0, s, lt, x, y, ma, mb, mc, partial);
     hipLaunchKernelGGL(k_loss_final, dim3(1), dim3(kFinal), 0, s, (const double *)partial, lt.total_tiles,
                        lt.inv_n, lt.lam, loss);
     if (grad)
-        hipLaunchKernelGGL(k_ssim_grad, dim3(lt.total_tiles), dim3(kThreads), 0, s, lt, x, y, (const float *)ma,
-                           (const float *)mb, (const float *)mc, grad);
+        hipLaunchKernelGGL(k_ssim_grad<CH>, dim3(lt.total_tiles), dim3(CH * kThreads), 0, s, lt, x, y,
+                           (const float *)ma, (const float *)mb, (const float *)mc, grad);
+}
+
+hipError_t launch_loss(const LossTable &lt, const float *x, const float *y, float *loss, float *grad, float *maps,
+                       double *partial, hipStream_t s) {
+    if (lt.total_tiles <= kGroupTiles)
+        loss_passes<3>(lt, x, y, loss, grad, maps, partial, s);
+    else
+        loss_passes<1>(lt, x, y, loss, grad, maps, partial, s);
     return hipGetLastError();
 }
 
