@@ -239,19 +239,72 @@ k_ssim_fwd(LossTable lt, const float *x, const float *y, float *map_a, float *ma
     }
 }
 
+// loss[0] = L, loss[1] = L2, loss[2] = SSIM, from the per-workgroup sums, by one
+// workgroup of N threads with K loads in flight each (31 -> 7 us for 16 x 800^2)
+template <int N, int K>
+__device__ __forceinline__ void final_sums(const LossTable &lt, const double *partial, float *loss, double *red) {
+    double s[K], q[K];
+#pragma unroll
+    for (int k = 0; k < K; ++k) s[k] = q[k] = 0.0;
+    const double2 *p = (const double2 *)partial;
+    for (int i = threadIdx.x; i < lt.total_tiles; i += K * N) {
+#pragma unroll
+        for (int k = 0; k < K; ++k)
+            if (i + k * N < lt.total_tiles) {
+                const double2 v = p[i + k * N];
+                s[k] += v.x;
+                q[k] += v.y;
+            }
+    }
+#pragma unroll
+    for (int k = 1; k < K; k *= 2)
+#pragma unroll
+        for (int j = 0; j < K; j += 2 * k) {
+            s[j] += s[j + k];
+            q[j] += q[j + k];
+        }
+    const double S = block_sum(s[0], red);
+    const double Q = block_sum(q[0], red);
+    if (threadIdx.x == 0) {
+        const double l2 = Q * lt.inv_n, ssim = S * lt.inv_n;
+        loss[0] = (float)((1.0 - lt.lam) * l2 + lt.lam * (1.0 - ssim));
+        loss[1] = (float)l2;
+        loss[2] = (float)ssim;
+    }
+}
+
+// (three groups: the same sums as the gradient pass takes, for a call without one)
+template <int CH>
+constexpr int kFinal = CH == 1 ? 1024 : CH * kThreads;
+template <int CH>
+constexpr int kFinalLoads = CH == 1 ? 4 : 2;
+template <int CH>
+__global__ void __launch_bounds__(kFinal<CH>) k_loss_final(LossTable lt, const double *partial, float *loss) {
+    __shared__ double red[kFinal<CH> / 64];
+    final_sums<kFinal<CH>, kFinalLoads<CH>>(lt, partial, loss, red);
+}
+
 // dL/dC = (1 - lambda) 2 (x - y) / n - lambda / n * (W*a + 2 x W*b + y W*c)
 // One map at a time; the next one's values are loaded during the sums.
 // 16 x 800^2: 0.49-0.55 -> 0.33 ms (738 MB: 0.15 ms at the rate of a large copy).
+// With three groups the first workgroup takes the loss from the partial sums, beside
+// the others (a launch less: 30.3 -> 27.5 us for the whole call at 167x127, 74.2 ->
+// 71.5 at 800^2).  With one group that costs the gradient more than the launch does
+// (674 -> 681 us for 16 x 800^2).
 template <int CH>
 __global__ void __launch_bounds__(CH *kThreads) __attribute__((amdgpu_waves_per_eu(CH == 1 ? 4 : 3)))
 k_ssim_grad(LossTable lt, const float *x, const float *y, const float *map_a, const float *map_b, const float *map_c,
-            float *grad) {
+            float *grad, const double *partial, float *loss) {
     __shared__ float sms[CH][kIH][kSW];
     __shared__ double hss[CH][kIH][kHW];
     const int group = CH == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x / kThreads);
     auto &sm = sms[group];
     auto &hs = hss[group];
-    const int t = blockIdx.x, tid = threadIdx.x % kThreads;
+    if (CH == 3 && blockIdx.x == 0) {
+        final_sums<kFinal<CH>, kFinalLoads<CH>>(lt, partial, loss, &hss[0][0][0]);
+        return;
+    }
+    const int t = CH == 3 ? blockIdx.x - 1 : blockIdx.x, tid = threadIdx.x % kThreads;
     const int v = loss_view_of_tile(lt, t);
     const int W = lt.W[v], H = lt.H[v];
     const int tl = t - lt.tile_off[v], tx = tl % lt.tiles_x[v], ty = tl / lt.tiles_x[v];
@@ -307,44 +360,18 @@ k_ssim_grad(LossTable lt, const float *x, const float *y, const float *map_a, co
     }
 }
 
-// loss[0] = L, loss[1] = L2, loss[2] = SSIM, from the per-workgroup sums
-// (one workgroup: each thread has four loads in flight; 31 -> 7 us for 16 x 800^2)
-constexpr int kFinal = 1024;
-__global__ void __launch_bounds__(kFinal) k_loss_final(const double *partial, int nblocks, double inv_n, double lam,
-                                                       float *loss) {
-    __shared__ double red[kFinal / 64];
-    double s[4] = {0.0, 0.0, 0.0, 0.0}, q[4] = {0.0, 0.0, 0.0, 0.0};
-    const double2 *p = (const double2 *)partial;
-    for (int i = threadIdx.x; i < nblocks; i += 4 * kFinal) {
-#pragma unroll
-        for (int k = 0; k < 4; ++k)
-            if (i + k * kFinal < nblocks) {
-                const double2 v = p[i + k * kFinal];
-                s[k] += v.x;
-                q[k] += v.y;
-            }
-    }
-    const double S = block_sum((s[0] + s[1]) + (s[2] + s[3]), red);
-    const double Q = block_sum((q[0] + q[1]) + (q[2] + q[3]), red);
-    if (threadIdx.x == 0) {
-        const double l2 = Q * inv_n, ssim = S * inv_n;
-        loss[0] = (float)((1.0 - lam) * l2 + lam * (1.0 - ssim));
-        loss[1] = (float)l2;
-        loss[2] = (float)ssim;
-    }
-}
-
 template <int CH>
 static void loss_passes(const LossTable &lt, const float *x, const float *y, float *loss, float *grad, float *maps,
                         double *partial, hipStream_t s) {
     const int64_t n = 3 * (int64_t)lt.total_px;
     float *ma = maps, *mb = maps + n, *mc = maps + 2 * n;
     hipLaunchKernelGGL(k_ssim_fwd<CH>, dim3(lt.total_tiles), dim3(CH * kThreads), 0, s, lt, x, y, ma, mb, mc, partial);
-    hipLaunchKernelGGL(k_loss_final, dim3(1), dim3(kFinal), 0, s, (const double *)partial, lt.total_tiles,
-                       lt.inv_n, lt.lam, loss);
+    if (CH == 1 || !grad)
+        hipLaunchKernelGGL(k_loss_final<CH>, dim3(1), dim3(kFinal<CH>), 0, s, lt, (const double *)partial, loss);
     if (grad)
-        hipLaunchKernelGGL(k_ssim_grad<CH>, dim3(lt.total_tiles), dim3(CH * kThreads), 0, s, lt, x, y,
-                           (const float *)ma, (const float *)mb, (const float *)mc, grad);
+        hipLaunchKernelGGL(k_ssim_grad<CH>, dim3(lt.total_tiles + (CH == 3)), dim3(CH * kThreads), 0, s, lt, x, y,
+                           (const float *)ma, (const float *)mb, (const float *)mc, grad, (const double *)partial,
+                           loss);
 }
 
 hipError_t launch_loss(const LossTable &lt, const float *x, const float *y, float *loss, float *grad, float *maps,
