@@ -6,7 +6,7 @@
 // E[y^2], E[xy]) under an 11x11 Gaussian window, zero outside the view, in
 // FP64: E[x^2] - mu_x^2 cancels, and FP64 vector arithmetic runs at the FP32
 // rate on this GPU.  A workgroup owns a 64x20 output tile of one view, one
-// channel at a time: it stages the tile plus a 5-pixel apron in LDS, then for
+// channel at a time (or, where tiles are few, each third of it one): it stages the tile plus a 5-pixel apron in LDS, then for
 // each moment sums the window rows into LDS (a thread takes eight neighbouring
 // outputs from 18 staged values) and the columns from there (a thread takes
 // five outputs below each other from 15).  The per-pixel SSIM and its
