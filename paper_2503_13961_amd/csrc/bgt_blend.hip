@@ -364,7 +364,9 @@ __device__ __forceinline__ int blocks_reached(const float4 &p, float sigma) {
 // point over the pixels of its disc by LDS atomics took a division, a square
 // root and an exponential per (point, pixel) instead of one per (run, pixel)
 // (16 x 800^2 forward: 0.98 -> 0.78 ms).
-// A list longer than the stage is taken in chunks.  DG: a second row of
+// A list longer than the stage is taken in chunks: only the last run of one can
+// go on in the next, with the smallest t so far, so that gamma* is that of the point
+// of smallest t over the whole list, as arg_min takes it.  DG: a second row of
 // zeros per extra row (the backward's dl/dgamma* sums), after the gamma* ones.
 template <int TS, int K, bool DG, typename BL>
 __device__ __forceinline__ RowInfo build_rows(BL &B, const StatePtrs &st, const RowPool &pool, int bs0, int bc, int ox,
@@ -374,6 +376,8 @@ __device__ __forceinline__ RowInfo build_rows(BL &B, const StatePtrs &st, const 
     const unsigned long long below = (1ull << lane) - 1ull;
     RowInfo R = {0, false, 0, false, false, nullptr};
     int nr = 0, nmap = RM;  // runs so far; rows with memory
+    int r_last = -1;        // the run taken last, its smallest t and the gamma of that point at this pixel
+    float t_last = 2.0f, g_last = 1.0f;
     if (bc == 0) {
         if (tid < NW) B.nmap[tid] = RM;
         __syncthreads();
@@ -460,11 +464,6 @@ __device__ __forceinline__ RowInfo build_rows(BL &B, const StatePtrs &st, const 
                         for (int i = 0; i < more; ++i) R.extra[(int64_t)(more + i) * 64 + lane] = 0.f;
                 }
             }
-            if (bc > CAP)  // rows are put together from several chunks
-                for (int i = 0; i < nmap; ++i) {
-                    if (i < RM) B.map[wave * RM + i][lane] = 1.0f;
-                    else R.extra[(int64_t)(i - RM) * 64 + lane] = 1.0f;
-                }
         }
         for (int r = first; r < R.n_runs; ++r) {
             int row = r;
@@ -476,8 +475,9 @@ __device__ __forceinline__ RowInfo build_rows(BL &B, const StatePtrs &st, const 
             const int rs = __builtin_amdgcn_readfirstlane(B.run_start[r]), re = __builtin_amdgcn_readfirstlane(B.run_start[r + 1]);
             const int s0 = max(rs - base, 0), s1 = min(re - base, n);
             if (s0 >= s1) continue;
-            float t = 2.0f;
-            int em = s0;
+            // (a run that the last chunk broke off goes on from its smallest t)
+            float t = r == r_last ? t_last : 2.0f, g = r == r_last ? g_last : 1.0f;
+            int em = -1;
             for (int e = s0; e < s1; e += 4) {  // (four reads in flight; a short run's last point is taken again)
                 float4 p[4];
 #pragma unroll
@@ -490,25 +490,13 @@ __device__ __forceinline__ RowInfo build_rows(BL &B, const StatePtrs &st, const 
                     t = less ? ti : t;
                 }
             }
-            float g = 1.0f;
-            if (t < kTOut) g = gamma_fn(sqrtf(point_d2(B.pt[em], lx, ly)), B.sigma[em]);  // (at most 1)
-            if (bc <= CAP) {
-                g = weight(g, __builtin_amdgcn_readfirstlane(B.run_prim[r]) == h);
-            } else {  // (from several chunks: gamma* until the last one)
-                g = fminf(g, row < RM ? B.map[wave * RM + row][lane] : R.extra[(int64_t)(row - RM) * 64 + lane]);
-            }
-            if (row < RM) B.map[wave * RM + row][lane] = g;
-            else R.extra[(int64_t)(row - RM) * 64 + lane] = g;
-        }
-    }
-    if (bc > CAP) {
-        for (int r = 0; r < R.n_runs; ++r) {
-            int row = r;
-            if constexpr (NW > 1) row = __builtin_amdgcn_readfirstlane((int)B.row_of[wave][r]);
-            if (row >= nmap) continue;
-            const bool own = __builtin_amdgcn_readfirstlane(B.run_prim[r]) == h;
-            if (row < RM) B.map[wave * RM + row][lane] = weight(B.map[wave * RM + row][lane], own);
-            else R.extra[(int64_t)(row - RM) * 64 + lane] = weight(R.extra[(int64_t)(row - RM) * 64 + lane], own);
+            if (em >= 0 && t < kTOut) g = gamma_fn(sqrtf(point_d2(B.pt[em], lx, ly)), B.sigma[em]);  // (at most 1)
+            r_last = r;
+            t_last = t;
+            g_last = g;
+            const float w = weight(g, __builtin_amdgcn_readfirstlane(B.run_prim[r]) == h);
+            if (row < RM) B.map[wave * RM + row][lane] = w;
+            else R.extra[(int64_t)(row - RM) * 64 + lane] = w;
         }
     }
     if (lane == 0) B.nmap[wave] = nmap;
