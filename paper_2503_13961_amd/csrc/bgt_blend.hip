@@ -19,6 +19,7 @@
 #include <type_traits>
 
 #include "bgt_internal.h"
+#include "bgt_nearest.h"
 #include "bgt_wave.h"
 
 namespace bgt {
@@ -151,17 +152,12 @@ constexpr int kNoRow = -1, kSearch = -2;
 // patch) lands there up to rounding, so distances below kDKink pixels count
 // as 0 for the position gradient
 constexpr float kDKink = 1e-6f;
-// Bound on |(d/sigma)^2 in FP32 - in FP64| below 1 for the staged boundary
-// points (offsets of at most a few pixels from their pixel centres, radii
-// >= 3 sqrt(0.3)): FP32 rounds the stored offsets and radius, the squared
-// distance and its ratio (d/sigma is within 4e-6, its square within twice
-// that, and the products add a few 1e-7).  Points whose FP32 values are within
-// twice this of the smallest are re-decided from the FP64 records.
+// Bound on |(d/sigma)^2 in FP32 - in FP64| below 1: d/sigma is within kRatioBand, its
+// square within twice that, and the products add a few 1e-7.
 constexpr float kTBand = 9e-6f;
 // A point is in range where d/sigma < 1; where (d/sigma)^2 in FP32 is within
 // 2 kTBand of 1 the ratio itself, the FP32 quotient, decides that.
 constexpr float kTIn = 1.0f - 2.0f * kTBand, kTOut = 1.0f + 2.0f * kTBand;
-constexpr float kRatioBand = 4e-6f;  // bound on |d/sigma in FP32 - in FP64| below 1, as kTBand
 
 // -log2(e)/2: G = exp(-d^T Q d / 2) = 2^(kE d^T Q d)
 constexpr float kE = -0.5f * 1.44269504088896341f;
@@ -220,22 +216,10 @@ __device__ __forceinline__ float weight(float gam, bool own) { return own ? gam 
 // The boundary point the gradient of gamma* goes to (Suppl. Sec. C, dl/db):
 // the minimiser of d/sigma among the points with d/sigma < 1, the lowest list
 // (raster) index among exactly equal ratios.  The FP32 pass finds the smallest
-// t = (d/sigma)^2 and the first point attaining it; when another point lies
-// within 2 kTBand of it, the order is decided again on the FP64 records of the
-// points in that band, which the generation pass keeps for every boundary
-// point, so the choice is the one exact arithmetic makes.
-struct ArgScan {
-    float t1 = 2.0f;  // smallest t, and the runner-up
-    float t2 = 2.0f;
-    int e1 = -1;
-    __device__ __forceinline__ void add(float t, int e) {
-        t2 = fminf(t2, fmaxf(t, t1));
-        if (t < t1) { t1 = t; e1 = e; }
-    }
-    __device__ __forceinline__ bool none() const { return !(t1 < kTOut); }
-    __device__ __forceinline__ bool ambiguous() const { return t2 - t1 <= 2.0f * kTBand; }
-    __device__ __forceinline__ bool edge() const { return t1 + 2.0f * kTBand >= kTIn; }  // (a near-tie can lie out of range)
-};
+// t = (d/sigma)^2 and the first point attaining it; when another point's ratio
+// is too close for FP32 to tell (ArgScan::near), the order is decided again on the
+// FP64 records of the points that close, which the generation pass keeps for
+// every boundary point, so the choice is the one exact arithmetic makes.
 
 // d/sigma in FP64 from pixel (x, y) to the boundary point of record bpix,
 // whose pixel is (bx, by) (same frame as x, y)
@@ -272,14 +256,15 @@ __device__ __forceinline__ int arg_min(const BL &B, const StatePtrs &st, int bs0
     }
     if (gam) {
         *gam = 1.0f;
-        if (!a.none()) {
+        if (a.t1 < kTOut) {
             const float4 p = boundary_point(st, (int)st.b_list[bs0 + a.e1], ox, oy, pm, sg);
             *gam = gamma_fn(sqrtf(point_d2(p, lx, ly)), sg);
         }
     }
-    if (a.none()) return -1;
-    if (a.edge()) {
-        // (rare) the points in range by their FP32 ratios, near-ties of those in FP64
+    if (!(a.t1 < kTOut)) return -1;
+    if (a.t1 + 2.0f * kTBand >= kTIn) {
+        // (rare) a near-tie can lie out of range: the points in range by their FP32
+        // ratios, near-ties of those in FP64
         float q1 = 2.0f, q2 = 2.0f;
         int first = -1, arg = -1;
         for (int pass = 0; pass < 2; ++pass) {
@@ -309,7 +294,7 @@ __device__ __forceinline__ int arg_min(const BL &B, const StatePtrs &st, int bs0
         const int bpix = (int)st.b_list[bs0 + e];
         const float4 p = boundary_point(st, bpix, ox, oy, pm, sg);
         const float t = point_t(p, lx, ly);
-        if (!(t <= a.t1 + 2.0f * kTBand)) continue;
+        if (!a.near(t)) continue;
         const int b = __float_as_int(p.w);
         const double q = ratio64(st, bpix, lx, ly, lo16(b), hi16(b));
         if (q < rb) { rb = q; arg = e; }
