@@ -207,9 +207,9 @@ bgt_status bgt_render_bwd(bgt_ctx *ctx, const bgt_prims *prims, const bgt_views 
  * [2] boundary pairs, [3] foreground pixels, [4] boundary pixels, [5] big
  * triangles (a bounding box over 256 pixels, or corners 2^17 pixels or more
  * apart on an axis), [6] tiles needing the global sort, [7] tiles whose boundary
- * list exceeded LDS, [8] tiles with more boundary runs (primitives) than
- * the forward keeps weights of in LDS (the others' rows lie in memory),
- * [9] reserved (0).  Returns BGT_E_OVERFLOW when any overflow flag is set
+ * list exceeded LDS, [8] tiles with an 8x8 block that more boundary runs
+ * (primitives) reach than the forward keeps weights of in LDS (the others' rows
+ * lie in memory), [9] reserved (0).  Returns BGT_E_OVERFLOW when any overflow flag is set
  * (and clears the context's record of it). */
 bgt_status bgt_query(bgt_ctx *ctx, const void *state, size_t state_bytes, int64_t *counters,
                      void *stream);

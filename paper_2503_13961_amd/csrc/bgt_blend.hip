@@ -92,6 +92,7 @@ struct BoundaryLds {
     int run_mask[NW > 1 ? NR : 1];  // the waves that the staged points of a run reach
     int ws[NW + 1];                 // the scan's wave totals
     int nmap[NW];                   // rows each wave has memory for
+    int far;                        // a wave has found more rows than fit LDS (larger tiles)
     float map[NW * RM][64];         // rows of w
     static_assert(NR <= 128, "row indices fit the entries' signed bytes");
 };
@@ -363,6 +364,7 @@ __device__ __forceinline__ RowInfo build_rows(BL &B, const StatePtrs &st, const 
     int nr = 0, nmap = RM;  // runs so far; rows with memory
     int r_last = -1;        // the run taken last, its smallest t and the gamma of that point at this pixel
     float t_last = 2.0f, g_last = 1.0f;
+    if (NW > 1 && tid == 0) B.far = 0;
     if (bc == 0) {
         if (tid < NW) B.nmap[tid] = RM;
         __syncthreads();
@@ -652,7 +654,9 @@ __global__ void __launch_bounds__(TS *TS) k_blend_fwd(Consts k, ViewTable vt, St
     pf.gp_next = (lane < KI && lane < gc) ? (int)st.g_list[gs0 + lane] : -1;
     pf.issue(st, gs0, gc, 0, lane, KI);
     const RowInfo R = build_rows<TS, K, false>(B, st, pool, bs0, bc, ox, oy, lx, ly, h);
-    if (R.n_runs > RM && tid == 0) atomicAdd((unsigned long long *)&st.counters[C_MANYRUNS], 1ull);
+    // (a tile counts once, by the first of its waves whose runs do not fit)
+    if (R.far && lane == 0 && (NW == 1 || atomicExch(&B.far, 1) == 0))
+        atomicAdd((unsigned long long *)&st.counters[C_MANYRUNS], 1ull);
     const float *const map = &B.map[wave * RM][lane];
 
     float T = 1.0f, C0 = 0.0f, C1 = 0.0f, C2 = 0.0f;

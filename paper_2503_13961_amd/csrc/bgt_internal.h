@@ -27,7 +27,7 @@ enum Counter {
     C_BIGBLIST = 7,
     C_ROWS_FWD = 8,   // gamma* rows handed out in memory by the forward, the backward
     C_ROWS_BWD = 9,
-    C_MANYRUNS = 10,  // tiles with more boundary runs than the forward's gamma* rows in LDS
+    C_MANYRUNS = 10,  // tiles with an 8x8 block that more boundary runs reach than the forward has rows for in LDS
     C_NUM = 16
 };
 // The per-wave foreground and boundary tallies go to kStripes slots 64 bytes
