@@ -44,7 +44,7 @@ def parse():
     ap.add_argument("--steps", type=int, default=20)
     ap.add_argument("--warmup", type=int, default=5)
     ap.add_argument("--tile", default="auto", help="8, 16, 32 or auto (the autotuner picks tile and batch)")
-    ap.add_argument("--batch", type=int, default=64, help="Gaussians per LDS batch when --tile is given")
+    ap.add_argument("--batch", type=int, default=64, help="with --tile: tells the two 8 px kernels apart (32, 64)")
     ap.add_argument("--workload", default="sphere2k_16v_800")
     ap.add_argument("--lattice", type=int, default=0,
                     help="time the lattice variant with this many Gaussians per sub-triangle edge (for profiling)")

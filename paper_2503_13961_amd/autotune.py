@@ -1,15 +1,15 @@
-"""Tile-size and LDS-batch autotuner for the batched renderer.
+"""Blend-kernel autotuner for the batched renderer.
 
-The blend kernels come in (tile, batch) variants: 8, 16 or 32 px square
-tiles, with 32, 64 or 128 Gaussians staged per LDS batch (at most one per
-pixel of the tile).  Which one is fastest depends on the Gaussians' screen
-size against the tile (pairs per Gaussian, boundary points per tile) and on
-how many tiles there are to fill the chip.  The tuner times one whole
-forward + backward per candidate on the caller's own scene and cameras and
-keeps the fastest.  Results are cached in a JSON file keyed by the GPU
-architecture, the Bezier degree, the patch count and the view sizes; the
-scene content is not part of the key, so a cached choice is a good guess for
-a scene of the same kind and size, not a measurement of it.
+The blend kernels come in four variants: tiles of 8 px with LDS for fewer
+boundary points and runs per tile (batch 32) or more (batch 64), and square
+tiles of 16 or 32 px, where every batch takes the same kernel.  Which one is
+fastest depends on the Gaussians' screen size against the tile (pairs per
+Gaussian, boundary points per tile) and on how many tiles there are to fill
+the chip.  The tuner times one whole forward + backward per variant on the
+caller's own scene and cameras and keeps the fastest.  Results are cached in a
+JSON file keyed by the GPU architecture, the Bezier degree, and the view sizes; the scene content is not part of the key, so
+a cached choice is a good guess for a scene of the same kind and size, not a
+measurement of it.
 """
 from __future__ import annotations
 
@@ -23,7 +23,8 @@ import torch
 
 from .render import Renderer, param_names
 
-CANDIDATES = ((8, 32), (8, 64), (16, 32), (16, 64), (16, 128), (32, 32), (32, 64), (32, 128))
+# (tile, batch), one pair per kernel
+CANDIDATES = ((8, 32), (8, 64), (16, 64), (32, 64))
 
 
 def default_cache_path() -> str:
