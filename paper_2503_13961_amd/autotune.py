@@ -7,7 +7,8 @@ fastest depends on the Gaussians' screen size against the tile (pairs per
 Gaussian, boundary points per tile) and on how many tiles there are to fill
 the chip.  The tuner times one whole forward + backward per variant on the
 caller's own scene and cameras and keeps the fastest.  Results are cached in a
-JSON file keyed by the GPU architecture, the Bezier degree, and the view sizes; the scene content is not part of the key, so
+JSON file keyed by the GPU architecture, the library's build, the Bezier degree,
+the patch count and the view sizes; the scene content is not part of the key, so
 a cached choice is a good guess for a scene of the same kind and size, not a
 measurement of it.
 """
@@ -21,6 +22,7 @@ import time
 import numpy as np
 import torch
 
+from . import native
 from .render import Renderer, param_names
 
 # (tile, batch), one pair per kernel
@@ -32,11 +34,17 @@ def default_cache_path() -> str:
                           os.path.join(os.path.expanduser("~"), ".cache", "bgt", "autotune.json"))
 
 
+def library_tag() -> str:
+    """Names the built library, so that a choice timed on other kernels is not taken for this one's."""
+    with open(native.LIB_PATH, "rb") as f:
+        return hashlib.sha1(f.read()).hexdigest()[:12]
+
+
 def shape_key(degree: int, num_prims: int, wh: np.ndarray, device: int = 0) -> str:
     arch = torch.cuda.get_device_properties(device).gcnArchName.split(":")[0]
     wh = np.ascontiguousarray(wh, dtype=np.int32).reshape(-1, 2)
     views = hashlib.sha1(wh.tobytes()).hexdigest()[:16]
-    return f"{arch}|n{degree}|P{num_prims}|V{len(wh)}|{views}"
+    return f"{arch}|{library_tag()}|n{degree}|P{num_prims}|V{len(wh)}|{views}"
 
 
 def _load(path):
