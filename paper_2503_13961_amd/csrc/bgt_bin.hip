@@ -5,10 +5,9 @@
 // (the high key digit) places each pair in its tile's segment, then each
 // segment is sorted on the low digits (depth, record index) or (primitive,
 // record index): by one wave in registers (a bitonic network over up to 512
-// keys), longer segments by a workgroup (runs of 64 keys sorted in registers,
-// merged pairwise by rank in LDS; segments beyond the LDS buffer: a bitonic
-// network in global memory).  The low digits make every key unique, so the
-// result does not depend on the order of the atomics that filled the segment.
+// keys), longer segments by a workgroup (see k_sort_long).  The low digits
+// make every key unique, so the result does not depend on the order of the
+// atomics that filled the segment.
 #include "bgt_internal.h"
 
 namespace bgt {
@@ -443,7 +442,7 @@ __global__ void __launch_bounds__(256) k_scatter_lattice(Consts k, ViewTable vt,
 // Ascending bitonic network whose first step of every merge compares mirrored
 // positions; positions >= n behave as +inf and never move, so a segment is
 // padded virtually to the next power of two.
-template <typename Get, typename CmpX>
+template <typename CmpX>
 __device__ __forceinline__ void bitonic_steps(int n2, CmpX cmpx) {
     for (int kk = 2; kk <= n2; kk <<= 1) {
         const int half = kk >> 1;
@@ -461,33 +460,6 @@ __device__ __forceinline__ void bitonic_steps(int n2, CmpX cmpx) {
             __syncthreads();
         }
     }
-}
-
-struct NoGet {};
-
-// Ascending bitonic sort of one key per lane across the wave (64 keys),
-// through lane exchanges only (no LDS, no barriers).
-__device__ __forceinline__ unsigned long long wave_sort64(unsigned long long x, int lane) {
-    for (int kk = 2; kk <= 64; kk <<= 1)
-        for (int j = kk >> 1; j >= 1; j >>= 1) {
-            const unsigned long long y = __shfl_xor(x, j, 64);
-            // the lower lane of a pair keeps the smaller key in ascending runs
-            const bool keep_min = ((lane & j) == 0) == ((lane & kk) == 0);
-            x = keep_min ? (y < x ? y : x) : (y < x ? x : y);
-        }
-    return x;
-}
-
-// Keys of the sorted a[0, n) below x (UPPER: not above x).
-template <bool UPPER>
-__device__ __forceinline__ int rank_in(const unsigned long long *a, int n, unsigned long long x) {
-    int lo = 0, hi = n;
-    while (lo < hi) {
-        const int mid = (lo + hi) >> 1;
-        if (UPPER ? a[mid] <= x : a[mid] < x) lo = mid + 1;
-        else hi = mid;
-    }
-    return lo;
 }
 
 // The list positions of tile t (of view v) under its slot: gpos[rec] is
@@ -905,7 +877,7 @@ __global__ void __launch_bounds__(256, 5) k_sort_long(ViewTable vt, StatePtrs st
         } else {
             int n2 = 1;
             while (n2 < cnt) n2 <<= 1;
-            bitonic_steps<NoGet>(n2, [&](int a, int b) {
+            bitonic_steps(n2, [&](int a, int b) {
                 if (b >= cnt) return;
                 const unsigned long long x = src[a], y = src[b];
                 if (y < x) { src[a] = y; src[b] = x; }

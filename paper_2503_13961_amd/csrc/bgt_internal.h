@@ -10,8 +10,6 @@ namespace bgt {
 
 // ---------------------------------------------------------------- sizes
 
-constexpr int kMaxL = 8;
-constexpr int kMaxNcp = (BGT_MAX_DEGREE + 1) * (BGT_MAX_DEGREE + 2) / 2;  // 21
 constexpr int kSortLds = 2048;        // per-tile list length sorted in LDS
 constexpr int kBigTriPixels = 256;    // bbox size above which a triangle is rasterized by a block
 
@@ -56,15 +54,6 @@ struct ViewTable {
     int32_t n, total_px, total_tiles, total_b8;  // total_b8: 8x8 pixel blocks over all views
     ViewInfo v[BGT_MAX_VIEWS];
 };
-
-__device__ __forceinline__ int view_of_pixel(const ViewTable &vt, int pix) {
-    int lo = 0, hi = vt.n - 1;
-    while (lo < hi) {
-        int mid = (lo + hi + 1) >> 1;
-        if (vt.v[mid].px_off <= pix) lo = mid; else hi = mid - 1;
-    }
-    return lo;
-}
 
 __device__ __forceinline__ int view_of_tile(const ViewTable &vt, int tile) {
     int lo = 0, hi = vt.n - 1;

@@ -54,8 +54,8 @@ __device__ __forceinline__ void rs_stage(float *v, int lane) {
 }
 
 // Reduce-scatter of N <= 64 per-lane values over the wave: afterwards lane l
-// holds in v[0] the wave total of value scatter_index(l) (0 when that index is
-// >= N).  About 3.4 operations per value instead of 6 per value for plain
+// holds in v[0] the wave total of the value whose index has the lane's bits 0, 1, 3,
+// 2, 4, 5 as bits 0 to 5 (0 when that index is >= N).  About 3.4 operations per value instead of 6 per value for plain
 // tree sums, and the totals land on distinct lanes, ready for one
 // multi-lane store or atomic.
 template <int N>
@@ -67,10 +67,6 @@ __device__ __forceinline__ void wave_reduce_scatter(float *v, int lane) {
     rs_stage<(N + 7) / 8, 2>(v, lane);
     rs_stage<(N + 15) / 16, 4>(v, lane);
     rs_stage<(N + 31) / 32, 5>(v, lane);
-}
-
-__device__ __forceinline__ int scatter_index(int lane) {
-    return (lane & 3) | (((lane >> 3) & 1) << 2) | (((lane >> 2) & 1) << 3) | (lane & 48);
 }
 
 }  // namespace bgt
