@@ -914,9 +914,13 @@ hipError_t launch_binning(const Consts &k, const ViewTable &vt, const StatePtrs 
     hipLaunchKernelGGL(k_sort_lists, dim3((unsigned)((2 * (int64_t)n + 3) / 4)), dim3(256), 0, s, vt, st,
                        lat_per_view, flag);
     // Tiles per workgroup of the long lists: one, so that no workgroup sorts
-    // several lists one after the other, up to kLongGroups tiles (twice as many
-    // workgroups, what the chip holds at once); beyond, more tiles, since nearly
-    // all of the workgroups would only find that they have no long list
+    // several lists one after the other, up to kLongGroups tiles; beyond, more
+    // tiles, since nearly all of the workgroups would only find that they have no
+    // long list.  The chip holds 1280 of these workgroups at once (five per CU by
+    // their registers), so the line is not where they all fit but a measured one, in
+    // us at 1 / 2 / 4 / 16 tiles per workgroup: 2500 tiles with long lists (8000
+    // cubic patches, 800x800, 16 px) 18 / 24 / - / 45, 3969 (the same at 1000x1000)
+    // 22 / 28 / 40 / 94, against 10000 with hardly any (2000 patches, 8 px) 12 / 7 / 5 / 5.
     int chunk = 1;
     while (chunk < kLongChunk && n / chunk > kLongGroups) chunk <<= 1;
     hipLaunchKernelGGL(k_sort_long, dim3((unsigned)((n + chunk - 1) / chunk), 2), dim3(256), 0, s, vt, st,
