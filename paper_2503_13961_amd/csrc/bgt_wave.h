@@ -69,4 +69,18 @@ __device__ __forceinline__ void wave_reduce_scatter(float *v, int lane) {
     rs_stage<(N + 31) / 32, 5>(v, lane);
 }
 
+// x of all lanes or'ed together (DPP shifts within 16-lane rows, then across
+// them), in every lane
+__device__ __forceinline__ unsigned wave_or(unsigned x) {
+#define BGT_OR(CTRL, ROWS) x |= (unsigned)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, ROWS, 0xF, true)
+    BGT_OR(0x111, 0xF);  // row_shr:1, 2, 4, 8
+    BGT_OR(0x112, 0xF);
+    BGT_OR(0x114, 0xF);
+    BGT_OR(0x118, 0xF);
+    BGT_OR(0x142, 0xA);  // row_bcast:15, 31
+    BGT_OR(0x143, 0xC);
+#undef BGT_OR
+    return (unsigned)__builtin_amdgcn_readlane((int)x, 63);
+}
+
 }  // namespace bgt
