@@ -176,6 +176,7 @@ k_ssim_fwd(LossTable lt, const float *x, const float *y, float *map_a, float *ma
     const int64_t base = lt.px_off[v], plane = lt.total_px;
     const int c0 = column_at(tid % kTW), r0 = tid / kTW * kVOut;
     const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const bool grads = map_a != nullptr;  // (no gradient wanted: no maps)
     double s_ssim = 0.0, s_sq = 0.0;
 #pragma unroll 1
     for (int c = group; c < 3; c += CH) {
@@ -221,6 +222,8 @@ k_ssim_fwd(LossTable lt, const float *x, const float *y, float *map_a, float *ma
             const double B1 = mx * mx + my * my + kSsimC1, B2 = B25[o];
             // S = A1 A2 / (B1 B2); S / A1 and S / A2 need no division of their own
             const double iB = 1.0 / (B1 * B2), SA1 = A2 * iB, SA2 = A1 * iB, S = A1 * SA1;
+            s_ssim += S;
+            if (!grads) continue;
             const double iB1 = B2 * iB, iB2 = B1 * iB;
             // dS/dmu_x, dS/dE[x^2], dS/dE[xy] with sigma_x^2 = E[x^2] - mu_x^2, sigma_xy = E[xy] - mu_x mu_y
             const double da = 2.0 * (my * (SA1 - SA2) + mx * S * (iB2 - iB1));
@@ -228,7 +231,6 @@ k_ssim_fwd(LossTable lt, const float *x, const float *y, float *map_a, float *ma
             ma[q] = (float)da;
             mb[q] = (float)(-S * iB2);
             mc[q] = (float)(2.0 * SA2);
-            s_ssim += S;
         }
     }
     const double a = block_sum(s_ssim, red);
@@ -365,7 +367,8 @@ static void loss_passes(const LossTable &lt, const float *x, const float *y, flo
                         double *partial, hipStream_t s) {
     const int64_t n = 3 * (int64_t)lt.total_px;
     float *ma = maps, *mb = maps + n, *mc = maps + 2 * n;
-    hipLaunchKernelGGL(k_ssim_fwd<CH>, dim3(lt.total_tiles), dim3(CH * kThreads), 0, s, lt, x, y, ma, mb, mc, partial);
+    hipLaunchKernelGGL(k_ssim_fwd<CH>, dim3(lt.total_tiles), dim3(CH * kThreads), 0, s, lt, x, y,
+                       grad ? ma : nullptr, mb, mc, partial);
     if (CH == 1 || !grad)
         hipLaunchKernelGGL(k_loss_final<CH>, dim3(1), dim3(kFinal<CH>), 0, s, lt, (const double *)partial, loss);
     if (grad)
