@@ -51,11 +51,14 @@ __device__ __forceinline__ T block_exclusive_scan(T x, T &total, T *lds_waves) {
 // The blend passes take the tiles with the longest Gaussian lists first: a
 // tile's time is proportional to its list, and a long one that starts last
 // leaves the chip waiting for it; a view's few hundred long lists also spread
-// evenly over the SIMDs.  (Raster order before: backward of 2000 patches' lattice
-// in 8 views of 800x800 1.40 -> 1.21 ms; 8 px tiles, 16 views of 800x800
-// 1.80 -> 1.69 ms, forward 0.78 -> 0.75; one such view, forward, 106 -> 85 us.
-// The order costs 2 us in the scan, 7 at 393000 tiles.)  Classes are an eighth of an octave wide (in raster
-// order within one, roughly), the longest class 0, empty lists last.
+// evenly over the SIMDs.  (Backward and forward in ms, raster order -> this one:
+// 2000 patches in 16 views of 800x800, 8 px tiles, 1.80 -> 1.73 and 0.775 -> 0.751,
+// their lattice at 16 px 2.02 -> 1.84 and 0.93 -> 0.84; 50,000 patches in 32 views of
+// 1024x768 3.97 -> 3.80 and 2.03 -> 1.91; one view of 800x800 0.214 -> 0.187 and 0.104
+// -> 0.084.  Giving each XCD runs of 64 consecutive places makes no difference: 1.727
+// and 1.727.  The order costs 2 us in the scan, 7 at 393000 tiles.)  Classes are an
+// eighth of an octave wide (in raster order within one, roughly), the longest class
+// 0, empty lists last.
 __device__ __forceinline__ int order_class(int len) {
     if (len < 8) return kOrderClasses - 1 - len;
     const int e = 31 - __clz(len);  // >= 3

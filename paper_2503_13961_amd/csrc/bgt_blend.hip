@@ -912,13 +912,7 @@ k_blend_bwd(Consts k, ViewTable vt, StatePtrs st, RowPool pool, const float *ima
     __shared__ int max_last;
     __shared__ int ring_done[RING], ring_free[RING];  // waves that finished a slot's batches; batches stored from it
     float *acc = U.loop.acc;  // (the batch's first entry's sums)
-    // At 8 px runs of 64 consecutive tiles of the order per XCD, many of them
-    // neighbours: the sums of a record's tiles then meet in one L2 more often (16
-    // views of 800x800 1.69 against 1.72 ms).  Larger tiles are too few for
-    // runs: the XCDs' first runs would be the longest lists (1.26 against 1.21 ms for
-    // the lattice of 2000 patches in 8 views).
-    const int place = TS == 8 ? xcd_runs<64>(blockIdx.x, gridDim.x) : (int)blockIdx.x;
-    const int t = st.order[place], tid = threadIdx.x, lane = tid & 63;
+    const int t = st.order[blockIdx.x], tid = threadIdx.x, lane = tid & 63;
     const int wave = NW > 1 ? __builtin_amdgcn_readfirstlane(tid >> 6) : 0;
     BatchLds<KI> &S = U.loop.S[wave];
     const int gc = st.g_count[t];
