@@ -10,9 +10,6 @@ namespace bgt {
 // the barycentric lattice of level R - 1 (index in the lattice order, a
 // outer).  (u, v) takes the linear interpolation of the three nodes of the
 // lattice triangle holding it; R = 1 is the single texel (weights 1, 0, 0).
-// A cell on the hypotenuse has the lower triangle only: a pixel at the patch's
-// rim, whose snapped edge reaches up to 1/512 px further than the patch, can lie
-// just past u + v = 1 and takes that triangle's nodes (extrapolated).
 template <typename T>
 __device__ __forceinline__ void theta_weights(int R, T u, T v, int *ti, T *tw) {
     // every output is a select, not a store under a branch, so that the
@@ -25,7 +22,7 @@ __device__ __forceinline__ void theta_weights(int R, T u, T v, int *ti, T *tw) {
     if (ia + ib > m - 1) ib = m - 1 - ia;  // on the hypotenuse
     const T fu = U - ia, fv = V - ib;
     auto node = [m](int a, int b) { return a * (m + 1) - a * (a - 1) / 2 + b; };
-    const bool one = R == 1, lower = ia + ib == m - 1 || fu + fv <= T(1);
+    const bool one = R == 1, lower = fu + fv <= T(1);
     ti[0] = one ? 0 : (lower ? node(ia, ib) : node(ia + 1, ib));
     ti[1] = one ? 0 : (lower ? node(ia + 1, ib) : node(ia, ib + 1));
     ti[2] = one ? 0 : (lower ? node(ia, ib + 1) : node(ia + 1, ib + 1));
