@@ -156,7 +156,7 @@ bgt_status make_shape(bgt_ctx *ctx, const bgt_prims *pr, const bgt_views *vw, Sh
         const int64_t vbytes = (int64_t)sizeof(VertRec) * vt.n * k.VL * k.P;
         sh.off[F_VERTS] = o;
         sh.patch_off = align256(o + vbytes);
-        sh.gsum_off = align256(sh.patch_off + 4 * (int64_t)k.pdw * k.P);
+        sh.gsum_off = align256(sh.patch_off + 4 * ((int64_t)k.pdw * k.P + kPatchTail));
         o = align256(sh.gsum_off + 4 * (int64_t)k.gdw * k.P);
     }
     put(F_GCOUNT, 4 * NT);

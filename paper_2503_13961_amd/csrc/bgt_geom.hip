@@ -173,11 +173,15 @@ hipError_t launch_tessellate(const Consts &k, const PrimPtrs &pr, float *verts, 
 // map, one rotation and scale per patch: R(q/|q|) diag(exp(log_scale)) and
 // r_b^2 = (r_ref / sharpness)^2 in FP64.
 // One thread (index idx) per word of a patch record, the patch index fastest
-// (the parameter arrays are read in runs of consecutive patches); the thread
-// of M's first word computes the rotation-scale setup and writes all 20 of its
-// words.
+// (the parameter arrays are read in runs of consecutive patches), and of the
+// records' tail; the thread of M's first word computes the rotation-scale setup
+// and writes all 20 of its words.
 __device__ __forceinline__ void prim_setup(const Consts &k, const PrimPtrs &pr, float *patch, int64_t idx) {
-    if (idx >= (int64_t)k.P * k.pdw) return;
+    const int64_t words = (int64_t)k.P * k.pdw;
+    if (idx >= words) {
+        if (idx < words + kPatchTail) patch[idx] = 0.f;
+        return;
+    }
     const int p = (int)(idx % k.P), i = (int)(idx / k.P);
     const int ncp = k.ncp, mo = patch_m_off(ncp), qo = patch_q_off(ncp);
     const int xo = patch_x_off(ncp), so = patch_sh_off(ncp, k.T);
@@ -308,7 +312,7 @@ __global__ void __launch_bounds__(256) k_front(Consts k, ViewTable vt, PrimPtrs 
 hipError_t launch_front(const Consts &k, const ViewTable &vt, const PrimPtrs &pr, const float *cams,
                         const StatePtrs &st, const ZeroTable &z, hipStream_t s) {
     const int64_t chunks = zero_total(z), per_view = (int64_t)k.VL * k.P;
-    const unsigned zb = zero_blocks(chunks), pb = (unsigned)(((int64_t)k.P * k.pdw + 255) / 256);
+    const unsigned zb = zero_blocks(chunks), pb = (unsigned)(((int64_t)k.P * k.pdw + kPatchTail + 255) / 256);
     // a point's evaluation is shared by four views where that leaves the chip
     // full (2^20 threads)
     const int views_per = per_view * vt.n >= ((int64_t)1 << 22) ? 4 : 1;

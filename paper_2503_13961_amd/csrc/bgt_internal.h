@@ -167,6 +167,11 @@ struct GradPtrs {
 __host__ __device__ constexpr int patch_dw(int ncp, int T = 1, int K = 0) {
     return (6 * ncp + 30 + (T > 1 || K > 0 ? 7 * T + 3 * K : 0) + 15) / 16 * 16;
 }
+// Words of 0 after the last record.  A rim pixel, which the snapped edge covers just
+// past u + v = 1, takes a fourth node of its texel cell, with a weight of that
+// excess; past a map's last node it reads the seven words after the texels, which
+// for degrees 1 and 2 reach up to three words past the record.
+constexpr int kPatchTail = 16;
 __host__ __device__ constexpr int patch_m_off(int ncp) { return 6 * ncp + 2; }
 __host__ __device__ constexpr int patch_q_off(int ncp) { return 6 * ncp + 22; }
 __host__ __device__ constexpr int patch_x_off(int ncp) { return 6 * ncp + 30; }
