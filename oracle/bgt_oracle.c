@@ -421,7 +421,8 @@ static int theta_weights(int R, double u, double v, int *ti, double *tw) {
     if (ib > m - 1) ib = m - 1;
     if (ia + ib > m - 1) ib = m - 1 - ia;   /* on the hypotenuse */
     double fu = U - ia, fv = V - ib;
-    if (fu + fv <= 1.0) {                   /* "up" lattice triangle */
+    if (ia + ib == m - 1 || fu + fv <= 1.0) {   /* "up" lattice triangle: a hypotenuse cell has no other, */
+                                                /* so a rim pixel just past u + v = 1 takes it too */
         ti[0] = lattice_index(m, ia, ib);     tw[0] = 1.0 - fu - fv;
         ti[1] = lattice_index(m, ia + 1, ib); tw[1] = fu;
         ti[2] = lattice_index(m, ia, ib + 1); tw[2] = fv;
