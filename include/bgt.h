@@ -184,7 +184,8 @@ bgt_status bgt_state_size(bgt_ctx *ctx, const bgt_prims *prims, const bgt_views 
  * g_list(u32), b_keys(u64), b_list(u32), gslot(f32x9 per record and tile
  * slot), gpos(i32 per record and tile slot), t_end(i32 per tile),
  * gwide(f32x9 per record), dbound(f32x3 per pixel), brec64(f64x3), big_tris,
- * scan, end. */
+ * scan, end.  After a pass g_keys and b_keys hold no keys: the blend passes
+ * keep rows of boundary weights there. */
 #define BGT_STATE_FIELDS 29
 bgt_status bgt_state_layout(bgt_ctx *ctx, const bgt_prims *prims, const bgt_views *views,
                             int64_t *offsets);

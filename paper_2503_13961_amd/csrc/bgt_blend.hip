@@ -38,9 +38,9 @@ namespace bgt {
 // of 1280 bytes: 5888 bytes (8 px, batch 32) and 7664 (batch 64) leave room for
 // 25 and 21 workgroups on a CU.  Searching the runs
 // without a row per pixel and Gaussian bound such scenes: the forward of 50,000
-// patches took 4.16 ms and takes 2.15, that of 8000 cubic patches at 1000x1000
-// and 16 px (rows per tile then, twelve in all) 2.25 and 0.25 ms, that of 64
-// patches at 128x128 and 16 px 2.37 and 0.14 ms.
+// patches took 4.16 ms and takes 1.91, that of 8000 cubic patches at 1000x1000
+// and 16 px (rows per tile then, twelve in all) 2.25 and 0.155 ms, that of 64
+// patches at 128x128 and 16 px 2.37 and 0.122 ms.
 template <int TS, int K>
 struct BlendDims {
     static constexpr int NW = TS * TS / 64;                          // waves
@@ -50,9 +50,10 @@ struct BlendDims {
     // one of them, with two barriers each, at which they waited for the
     // slowest: forward of 2000 patches' lattice in 8 views of 800x800 0.96 ->
     // 0.77 ms, 8000 cubic patches at 1000x1000 0.245 -> 0.19 ms; 32 px tiles,
-    // four views of 800x800, 1.34 -> 0.57 ms.)  64 entries fill the loaders'
-    // lanes (16 px, 32 entries: 0.80 ms for the lattice), 32 keep a fifth
-    // wave per SIMD at 8 px and in the backward.
+    // four views of 800x800, 1.34 -> 0.57 ms; 0.43, 0.155 and 0.50 with the tile
+    // order and own_prims.)  64 entries fill the loaders' lanes (16 px, 32
+    // entries: 0.80 against 0.77 ms for the lattice), 32 keep a fifth wave per SIMD
+    // at 8 px and in the backward.
     static constexpr int KI_FWD = TS == 8 ? 32 : 64;
     static constexpr int KI_BWD = 32;
     static constexpr int CAP = TS >= 32 ? 512 : (TS >= 16 ? 256 : (K > 32 ? 112 : 88));
@@ -363,7 +364,7 @@ __device__ __forceinline__ int blocks_reached(const float4 &p, float sigma) {
 // run's points at its own pixel, a dozen instructions per point: scattering each
 // point over the pixels of its disc by LDS atomics took a division, a square
 // root and an exponential per (point, pixel) instead of one per (run, pixel)
-// (16 x 800^2 forward: 0.98 -> 0.78 ms).
+// (16 x 800^2 forward: 0.98 -> 0.78 ms; 0.75 now).
 // A list longer than the stage is taken in chunks: only the last run of one can
 // go on in the next, with the smallest t so far, so that gamma* is that of the point
 // of smallest t over the whole list, as arg_min takes it.  DG: a second row of
@@ -867,13 +868,15 @@ __device__ __forceinline__ void route_boundary(const StatePtrs &st, int bpix, fl
 // atomics instead); larger tiles add their waves' totals in LDS first, in a
 // ring of batches, each stored by the last wave to finish it: with a barrier
 // per 64 entries the waves waited for the slowest a third of the time (four
-// views of 800x800, 16 px tiles: 0.92 -> 0.78 ms, 32 px 2.6 -> 2.2 ms).
+// views of 800x800, 16 px tiles: 0.92 -> 0.78 ms, 32 px 2.6 -> 2.2 ms; 0.69 and 1.57
+// now).
 // The boundary terms accumulate per (row, pixel), as the sum of dl/dw, in
 // registers for the LDS rows (the row is wave-uniform), and go to the
 // minimising boundary point at the end.  16 views of 800x800, 2000 patches, 8 px
-// tiles: 2.25 -> 1.80 ms, 1.43e9 -> 0.94e9 VALU instructions; 50,000 patches at
-// 32 x 1024x768: 7.35 -> 4.11 ms (with the rows above); 8000 cubic patches at
-// 1000x1000, 16 px tiles: 3.39 -> 0.43 ms (rows per 8x8 block).
+// tiles: 2.25 -> 1.80 ms, 1.43e9 -> 0.94e9 VALU instructions (1.73 ms now); 50,000
+// patches at 32 x 1024x768: 7.35 -> 4.11 ms (with the rows above; 3.80 now); 8000
+// cubic patches at 1000x1000, 16 px tiles: 3.39 -> 0.43 ms (rows per 8x8 block;
+// 0.34 now).
 // Waves per SIMD the registers must allow.
 template <int TS, int K>
 struct BwdWaves {

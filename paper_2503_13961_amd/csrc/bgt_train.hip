@@ -157,7 +157,7 @@ struct StageRows {
 };
 
 // Window moments, SSIM and its derivative maps; per-workgroup sums of the
-// SSIM map and of the squared error.  16 x 800^2: 0.67-0.75 -> 0.42 ms (615 MB:
+// SSIM map and of the squared error.  16 x 800^2: 0.67-0.75 -> 0.36-0.45 ms (615 MB:
 // 0.12 ms at the rate of a large copy; FP64 issue alone 0.21).
 template <int CH>
 __global__ void __launch_bounds__(CH *kThreads) __attribute__((amdgpu_waves_per_eu(CH == 1 ? 4 : 3)))
@@ -288,7 +288,7 @@ __global__ void __launch_bounds__(kFinal<CH>) k_loss_final(LossTable lt, const d
 
 // dL/dC = (1 - lambda) 2 (x - y) / n - lambda / n * (W*a + 2 x W*b + y W*c)
 // One map at a time; the next one's values are loaded during the sums.
-// 16 x 800^2: 0.49-0.55 -> 0.33 ms (738 MB: 0.15 ms at the rate of a large copy).
+// 16 x 800^2: 0.49-0.55 -> 0.30-0.35 ms (738 MB: 0.15 ms at the rate of a large copy).
 // With three groups the first workgroup takes the loss from the partial sums, beside
 // the others (a launch less: 30.3 -> 27.5 us for the whole call at 167x127, 74.2 ->
 // 71.5 at 800^2).  With one group that costs the gradient more than the launch does
