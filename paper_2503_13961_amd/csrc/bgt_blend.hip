@@ -91,9 +91,8 @@ struct BoundaryLds {
     int run_start[NR + 1];  // first point of each run, a position in the tile's list
     uint8_t row_of[NW > 1 ? NW : 1][NW > 1 ? NR : 1];  // each wave's row of a run (255: the run does not reach its block)
     int run_mask[NW > 1 ? NR : 1];  // the waves that the staged points of a run reach
-    int ws[NW + 1];                 // the scan's wave totals
+    int ws[NW + 1];                 // the scan's wave totals; last: a wave has found more rows than fit LDS
     int nmap[NW];                   // rows each wave has memory for
-    int far;                        // a wave has found more rows than fit LDS (larger tiles)
     float map[NW * RM][64];         // rows of w
     static_assert(NR <= 128, "row indices fit the entries' signed bytes");
 };
@@ -379,7 +378,7 @@ __device__ __forceinline__ RowInfo build_rows(BL &B, const StatePtrs &st, const 
     int nr = 0, nmap = RM;  // runs so far; rows with memory
     int r_last = -1;        // the run taken last, its smallest t and the gamma of that point at this pixel
     float t_last = 2.0f, g_last = 1.0f;
-    if (NW > 1 && tid == 0) B.far = 0;
+    if (NW > 1 && !DG && tid == 0) B.ws[NW] = 0;
     if (bc == 0) {
         if (tid < NW) B.nmap[tid] = RM;
         __syncthreads();
@@ -595,7 +594,10 @@ __device__ __forceinline__ int stage_slot(BatchLds<KI> &S, const SlotPrefetch &P
     const float thr = sub_block_bound(P.r0.z, P.r0.w, P.r1.x, kappa);
     S.e[kk] = ex;
     S.c[kk] = make_float4(P.r1.y, P.r1.z, P.r1.w, 0.0f);
+    const float2 m = make_float2((float)x + P.r0.x, (float)y + P.r0.y);
+    const int bits = sub_blocks(m, ex, thr, __float_as_int(P.r3.x), __float_as_int(P.r3.y), wx0, wy0);
     const int g = __float_as_int(P.r2.y);
+    const int own_bits = (own >> (g & 63)) & 1ull ? bits : 0;  // without a row
     const int r = find_run(B.run_prim, R.n_runs, g);
     int row = R.many && g > B.run_prim[BL::NR - 1] ? kSearch : kNoRow;
     if (r >= 0) {
@@ -606,11 +608,9 @@ __device__ __forceinline__ int stage_slot(BatchLds<KI> &S, const SlotPrefetch &P
             row = row == 255 ? kNoRow : (row < B.nmap[wave] ? row : kSearch);
         }
     }
-    const float2 m = make_float2((float)x + P.r0.x, (float)y + P.r0.y);
     S.mp[kk].m = m;
     S.mp[kk].pr = make_int2(g, row);
-    const int bits = sub_blocks(m, ex, thr, __float_as_int(P.r3.x), __float_as_int(P.r3.y), wx0, wy0);
-    return row != kNoRow || ((own >> (g & 63)) & 1ull) ? bits : 0;
+    return row != kNoRow ? bits : own_bits;
 }
 
 // Between a wave's writes and reads of its own batch (its LDS accesses
@@ -671,7 +671,7 @@ __global__ void __launch_bounds__(TS *TS) k_blend_fwd(Consts k, ViewTable vt, St
     pf.issue(st, gs0, gc, 0, lane, KI);
     const RowInfo R = build_rows<TS, K, false>(B, st, pool, bs0, bc, ox, oy, lx, ly, h);
     // (a tile counts once, by the first of its waves whose runs do not fit)
-    if (R.far && lane == 0 && (NW == 1 || atomicExch(&B.far, 1) == 0))
+    if (R.far && lane == 0 && (NW == 1 || atomicExch(&B.ws[NW], 1) == 0))
         atomicAdd((unsigned long long *)&st.counters[C_MANYRUNS], 1ull);
     const float *const map = &B.map[wave * RM][lane];
 
