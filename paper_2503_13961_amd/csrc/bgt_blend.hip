@@ -169,18 +169,18 @@ constexpr float kE = -0.5f * 1.44269504088896341f;
 // transmittance bit for bit.
 __device__ __forceinline__ float support_exp2(float e) { return __builtin_amdgcn_exp2f(e); }
 
-// The primitives of a block's pixels, their ids mod 64 as bits: an entry of another
+// The primitives of a block's pixels, their ids mod 32 as bits: an entry of another
 // primitive without a row has w = 0 on the whole block and is left out of the
 // batch's mask.  (A primitive that shares the bit of one of them stays in and is
 // dropped at its pixels.)  Lists of wide Gaussians are mostly such entries, and every
 // wave walked them: one 256x256 view of 64 patches, Gaussians of 20 px, 16 px tiles,
 // backward 2.97 -> 1.96 ms (2.51 with batches shared by the waves of a tile),
 // forward 2.98 -> 2.01; lattice of 2000 patches in 8 views of 800x800, step 2.62 ->
-// 2.13 ms; 16 views of 800x800 at 8 px 3.35 -> 3.31.
-__device__ __forceinline__ unsigned long long own_prims(int h) {  // h: each lane's primitive, -1: none
-    const unsigned bit = h >= 0 ? 1u << (h & 31) : 0u;
-    const unsigned lo = wave_or(h & 32 ? 0u : bit), hi = wave_or(h & 32 ? bit : 0u);
-    return (unsigned long long)hi << 32 | lo;
+// 2.14 ms; 16 views of 800x800 at 8 px 3.34 -> 3.30.  (With 64 bits the lattice's forward
+// is 2 % faster and those of 16 views and of 20,000 cubic patches 0.5 and 1 % slower: a
+// bit of 64 takes five instructions where one of 32 takes one.)
+__device__ __forceinline__ unsigned own_prims(int h) {  // h: each lane's primitive, -1: none
+    return wave_or(h >= 0 ? 1u << (h & 31) : 0u);
 }
 
 // run index of primitive g among the tile's runs, -1 when absent
@@ -586,7 +586,7 @@ __device__ __forceinline__ float sub_block_bound(float qa, float qb, float qc, f
 // starts at (wx0, wy0); returns the entry's sub_blocks (none where w = 0 on the block).
 template <int KI, typename BL>
 __device__ __forceinline__ int stage_slot(BatchLds<KI> &S, const SlotPrefetch &P, int kk, int wx0, int wy0, const BL &B,
-                                          const RowInfo &R, unsigned long long own, float kappa, int wave) {
+                                          const RowInfo &R, unsigned own, float kappa, int wave) {
     // the pixel the Gaussian's mean is stored against
     const int a = __float_as_int(P.r2.w);
     const int x = lo16(a) - wx0, y = hi16(a) - wy0;
@@ -597,7 +597,6 @@ __device__ __forceinline__ int stage_slot(BatchLds<KI> &S, const SlotPrefetch &P
     const float2 m = make_float2((float)x + P.r0.x, (float)y + P.r0.y);
     const int bits = sub_blocks(m, ex, thr, __float_as_int(P.r3.x), __float_as_int(P.r3.y), wx0, wy0);
     const int g = __float_as_int(P.r2.y);
-    const int own_bits = (own >> (g & 63)) & 1ull ? bits : 0;  // without a row
     const int r = find_run(B.run_prim, R.n_runs, g);
     int row = R.many && g > B.run_prim[BL::NR - 1] ? kSearch : kNoRow;
     if (r >= 0) {
@@ -610,7 +609,7 @@ __device__ __forceinline__ int stage_slot(BatchLds<KI> &S, const SlotPrefetch &P
     }
     S.mp[kk].m = m;
     S.mp[kk].pr = make_int2(g, row);
-    return row != kNoRow ? bits : own_bits;
+    return bits & (row != kNoRow ? -1 : __builtin_amdgcn_sbfe((int)own, g, 1));  // (bit g mod 32, as 0 or -1)
 }
 
 // Between a wave's writes and reads of its own batch (its LDS accesses
@@ -680,7 +679,7 @@ __global__ void __launch_bounds__(TS *TS) k_blend_fwd(Consts k, ViewTable vt, St
     int last = gc;
     const float amax = k.alpha_max, tmin = k.t_min;
     const bool nob = (k.flags & BGT_FLAG_NO_BOUNDARY) != 0;
-    const unsigned long long own_m = nob ? ~0ull : own_prims(h);
+    const unsigned own_m = nob ? ~0u : own_prims(h);
     const bool far = R.far;  // only then do the loops below look for entries without an LDS row
     // support test d^T Q d <= 2 ln(1/g_min) as a base-2 exponent: G = 2^e, e >= log2(g_min)
     const float e_min = kE * k.kappa2;
@@ -981,7 +980,7 @@ k_blend_bwd(Consts k, ViewTable vt, StatePtrs st, RowPool pool, const float *ima
     const float amax = k.alpha_max;
     const bool nob = (k.flags & BGT_FLAG_NO_BOUNDARY) != 0;
     const LaneMask nob_m = nob ? ~0ull : 0ull;
-    const unsigned long long own_m = nob ? ~0ull : own_prims(h);
+    const unsigned own_m = nob ? ~0u : own_prims(h);
     const float e_min = kE * k.kappa2;
     const float kappa = sqrtf(k.kappa2);
     // pixel i of this lane's row's sub-block in each of the four: its place in

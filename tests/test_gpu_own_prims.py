@@ -1,7 +1,7 @@
 """Wide Gaussians of other patches, which a block leaves out of its batches where
 none of its pixels shows their patch and no boundary point of theirs is near:
-patches that share a bit of the block's set (ids 64 apart), a set of more than
-64 patches, a block of background, and the variant without coefficients, where
+patches that share a bit of the block's set (ids 32 apart), a set of more than
+32 patches, a block of background, and the variant without coefficients, where
 nothing may be left out.  Images and gradients against the oracle."""
 import numpy as np
 import pytest
@@ -14,7 +14,7 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("tile", [8, 16, 32])
-@pytest.mark.parametrize("P,flags", [(2, 0), (65, 0), (150, 0), (65, 1)])
+@pytest.mark.parametrize("P,flags", [(2, 0), (33, 0), (65, 0), (150, 0), (65, 1)])
 def test_wide_gaussians_of_other_patches(tile, P, flags):
     G.log(f"[own] tile={tile} P={P} flags={flags}")
     sc = S.random_triangles(P=P, degree=2, seed=P + 1)
